@@ -135,6 +135,10 @@ struct DkdvCfg {
   // per stage: Q tile, dO tile, lse2[BQ], D[BQ]
   static constexpr int STAGE = 2 * QTILE * 2 + 2 * BQ * 4;
   static constexpr int LDS_BYTES = 2 * STAGE + KTILE * 2;
+  // 32-column blocks of a gradient turned at a time (store_rows_f32)
+  static constexpr int F32_PASS = D / 32;
+  static_assert(NW * F32_PASS * kF32Block * 4 <= LDS_BYTES,
+                "the gradients are turned in the tile buffers");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
 
@@ -416,34 +420,21 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
     }
   }
 
-  // every copy this wave issued has landed before the workgroup ends (a part
-  // with no query steps still issued its K copies)
+  // every copy this wave issued has landed (a part with no query steps still
+  // issued its K copies) and every wave is done with the tiles before the
+  // gradients are turned in their place
   wait_dma();
-  if (key < k_hi) {
+  __syncthreads();
+  {
     const bool split = a.split_kv.parts > 1;
-    const size_t off = (size_t)key * kvstride + (size_t)hk * D;
+    const size_t off = (size_t)kw0 * kvstride + (size_t)hk * D;
     const size_t poff = (size_t)part * (a.chunked ? a.tk : a.total_tokens) * kvstride + off;
-    float* dkp = split ? a.part_dk + poff : a.dk + off;
-    float* dvp = split ? a.part_dv + poff : a.dv + off;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        const int d0 = db * 32 + grp * 8 + hh * 4;
-        f32x4 kv, vv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = grp * 4 + e;
-          kv[e] = dka[db][r] * a.scale;
-          vv[e] = dva[db][r];
-        }
-        if (a.accumulate && !split) {
-          kv += *reinterpret_cast<const f32x4*>(dkp + d0);
-          vv += *reinterpret_cast<const f32x4*>(dvp + d0);
-        }
-        *reinterpret_cast<f32x4*>(dkp + d0) = kv;
-        *reinterpret_cast<f32x4*>(dvp + d0) = vv;
-      }
+    float* lds = reinterpret_cast<float*>(smem) + w * C::F32_PASS * kF32Block;
+    const bool add = a.accumulate && !split;
+    store_rows_f32<D, C::F32_PASS>(dka, a.scale, split ? a.part_dk + poff : a.dk + off, kvstride,
+                                   k_hi - kw0, add, lds);
+    store_rows_f32<D, C::F32_PASS>(dva, 1.f, split ? a.part_dv + poff : a.dv + off, kvstride,
+                                   k_hi - kw0, add, lds);
   }
 }
 
@@ -457,6 +448,10 @@ struct DqCfg {
   static constexpr int KTILE = KL::elems(BK);
   static constexpr int VTILE = VL::elems(BK);
   static constexpr int LDS_BYTES = 2 * (KTILE + VTILE) * 2;
+  // 32-column blocks of dQ turned at a time (store_rows_f32)
+  static constexpr int F32_PASS = NW * (D / 32) * kF32Block * 4 <= LDS_BYTES ? D / 32 : 1;
+  static_assert(NW * F32_PASS * kF32Block * 4 <= LDS_BYTES,
+                "dQ is turned in the tile buffers");
 };
 
 template <int D, int NW>
@@ -659,25 +654,18 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
       });
       if (!ran && more) issue(it + 1);
     }
-    // the last tile's empty-range copies land before the workgroup ends
+    // the last tile's empty-range copies have landed and every wave is done
+    // with the tiles before dQ is turned in their place
     wait_dma();
+    __syncthreads();
   }
 
-  if (row < seg_hi) {
-    const bool split = a.split_q.parts > 1;
-    const size_t off = (size_t)row * qstride + (size_t)h * D;
-    float* dqp = split ? a.part_dq + (size_t)part * a.total_tokens * qstride + off : a.dq + off;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        const int d0 = db * 32 + grp * 8 + hh * 4;
-        f32x4 v = {dqa[db][grp * 4] * a.scale, dqa[db][grp * 4 + 1] * a.scale,
-                   dqa[db][grp * 4 + 2] * a.scale, dqa[db][grp * 4 + 3] * a.scale};
-        if (a.accumulate && !split) v += *reinterpret_cast<const f32x4*>(dqp + d0);
-        *reinterpret_cast<f32x4*>(dqp + d0) = v;
-      }
-  }
+  const bool split = a.split_q.parts > 1;
+  const size_t off = (size_t)wrow0 * qstride + (size_t)h * D;
+  store_rows_f32<D, C::F32_PASS>(
+      dqa, a.scale, split ? a.part_dq + (size_t)part * a.total_tokens * qstride + off : a.dq + off,
+      qstride, seg_hi - wrow0, a.accumulate && !split,
+      reinterpret_cast<float*>(smem) + w * C::F32_PASS * kF32Block);
 }
 
 }  // namespace pdy

@@ -334,6 +334,121 @@ __device__ __forceinline__ void wait_dma_n() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
 }
 
+// ---------------------------------------------------------------------------
+// Output tiles.  An accumulator tile has one row (query or key) per lane, so a
+// store straight from it writes 16 or 32 bytes to each of 32 rows per
+// instruction, and the L2 channels, which take about one request per clock
+// each, bound a workgroup's end (256 workgroups of 64 KB of bf16 rows: about
+// 4 us).  The wave instead turns its 32 rows through LDS, so that every store
+// instruction writes whole 128-byte lines (forward + backward, one sequence:
+// 2,500 tokens x 6/2 heads 117.5 -> 112.6 us, 4,096 x 4 146.9 -> 142.5;
+// 32 x 512 tokens x 16 heads of 64 274 -> 262; packed 65,536 x 32 heads 10.13 ->
+// 10.00 ms; 131,072 x 4 unchanged).
+// The caller has passed a workgroup barrier since the tile buffers in `lds`
+// were last read.  A wave's LDS operations complete in order, so its own reads
+// need no barrier after its writes; the fences keep the compiler's order.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+// Four 16-byte LDS reads STEP bytes apart, waited for.
+template <int OFF, int STEP>
+__device__ __forceinline__ void lds_read4(uint32_t addr, u32x4 (&v)[4]) {
+  static_assert(OFF + 3 * STEP < 65536, "LDS offset out of range");
+  asm volatile(
+      "ds_read_b128 %0, %4 offset:%5\n\t"
+      "ds_read_b128 %1, %4 offset:%6\n\t"
+      "ds_read_b128 %2, %4 offset:%7\n\t"
+      "ds_read_b128 %3, %4 offset:%8\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+      : "v"(addr), "i"(OFF), "i"(OFF + STEP), "i"(OFF + 2 * STEP), "i"(OFF + 3 * STEP)
+      : "memory");
+}
+
+// One wave's 32 rows of D floats, acc * mul (mul: this lane's row's factor), to
+// dst (row 0, column 0; `stride` floats from row to row), rows < nrows only;
+// accumulate: added to what dst holds.  A 32-column block takes kF32Pitch floats
+// a row in LDS (rows 16 bytes apart in the banks: conflict-free both ways).
+// PASS blocks are turned at a time: PASS * kF32Block floats of LDS per wave.
+constexpr int kF32Pitch = 36;
+constexpr int kF32Block = 32 * kF32Pitch;
+template <int D, int PASS>
+__device__ __forceinline__ void store_rows_f32(const f32x16 (&acc)[D / 32], float mul, float* dst,
+                                               size_t stride, int nrows, bool accumulate,
+                                               float* lds) {
+  static_assert((D / 32) % PASS == 0, "whole passes");
+  const int l = __lane_id();
+  const int wr = (l & 31) * kF32Pitch + (l >> 5) * 4;  // write: this lane's row
+  const int rr = l >> 3, c = (l & 7) * 4;              // read: 8 lanes a row
+  const uint32_t rd = lds_addr(lds) + (rr * kF32Pitch + c) * 4;
+  static_for<D / 32 / PASS>([&](auto Pass) {
+    constexpr int p = decltype(Pass)::value * PASS;
+#pragma unroll
+    for (int b = 0; b < PASS; ++b)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x16& x = acc[p + b];
+        *reinterpret_cast<f32x4*>(lds + b * kF32Block + wr + g * 8) =
+            f32x4{x[g * 4] * mul, x[g * 4 + 1] * mul, x[g * 4 + 2] * mul, x[g * 4 + 3] * mul};
+      }
+    wave_lds_fence();
+    static_for<PASS>([&](auto B) {
+      constexpr int b = decltype(B)::value;
+      u32x4 raw[4];
+      lds_read4<b * kF32Block * 4, 8 * kF32Pitch * 4>(rd, raw);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = i * 8 + rr;
+        f32x4 v = __builtin_bit_cast(f32x4, raw[i]);
+        float* to = dst + (size_t)r * stride + (p + b) * 32 + c;
+        if (r < nrows) {
+          if (accumulate) v += *reinterpret_cast<const f32x4*>(to);
+          *reinterpret_cast<f32x4*>(to) = v;
+        }
+      }
+    });
+  });
+}
+
+// The same in bf16 (rounded to nearest even): kBf16Pitch<D> elements a row in
+// LDS, 32 rows per wave.
+template <int D>
+constexpr int kBf16Pitch = D + 8;
+template <int D>
+__device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[D / 32], float mul,
+                                                uint16_t* dst, size_t stride, int nrows,
+                                                uint16_t* lds) {
+  constexpr int P = kBf16Pitch<D>, LANES = D / 8, ROWS = 64 / LANES;
+  const int l = __lane_id();
+  const int wr = (l & 31) * P + (l >> 5) * 4;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x16& x = acc[db];
+      const f32x2 v01 = {x[g * 4] * mul, x[g * 4 + 1] * mul};
+      const f32x2 v23 = {x[g * 4 + 2] * mul, x[g * 4 + 3] * mul};
+      *reinterpret_cast<u32x2*>(lds + wr + db * 32 + g * 8) =
+          u32x2{__builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2)),
+                __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2))};
+    }
+  wave_lds_fence();
+  const int rr = l / LANES, c = (l % LANES) * 8;
+  const uint32_t rd = lds_addr(lds) + (rr * P + c) * 2;
+  static_for<32 / ROWS / 4>([&](auto I) {
+    constexpr int i0 = decltype(I)::value * 4;
+    u32x4 v[4];
+    lds_read4<i0 * ROWS * P * 2, ROWS * P * 2>(rd, v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = (i0 + i) * ROWS + rr;
+      if (r < nrows) *reinterpret_cast<u32x4*>(dst + (size_t)r * stride + c) = v[i];
+    }
+  });
+}
+
 // Work schedule built by plan_kernel: items are (segment, level) pairs with
 // level j meaning "tile j of the segment" (forward / dQ) or "tile nt-1-j"
 // (dK/dV); a higher level is a heavier causal tile.  Two orders of the same

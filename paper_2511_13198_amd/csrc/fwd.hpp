@@ -54,6 +54,11 @@ struct FwdCfg {
   // K/V tiles in flight: the direct copies run STAGES-1 tiles ahead
   static constexpr int STAGES = PDY_FWD_STAGES;
   static constexpr int LDS_BYTES = STAGES * (KTILE + VTILE) * 2;
+  // 32-column blocks of the fp32 partial O turned at a time (store_rows_f32)
+  static constexpr int F32_PASS = D == 128 ? 4 : 1;
+  static_assert(NW * F32_PASS * kF32Block * 4 <= LDS_BYTES &&
+                    NW * 32 * kBf16Pitch<D> * 2 <= LDS_BYTES,
+                "the output tile is turned in the tile buffers");
 };
 
 struct FwdArgs {
@@ -89,46 +94,35 @@ struct FwdArgs {
 // key offset within a 32-key block held in accumulator register r (lane half 0)
 __device__ __forceinline__ constexpr int acc_row_off(int r) { return (r >> 2) * 8 + (r & 3); }
 
-// Epilogue of a forward workgroup's wave: normalise its 32 rows and write O
-// (bf16) and LSE (natural log), or, for a split-K part, the part's fp32 O and
-// LSE.  A row that saw no key (possible for a chunk or a part) gets O = 0 and
-// LSE = -inf.  m: the base-2 exponent offset; lsum: this lane's partial row
-// sum (the other half of the row's keys is on lane l ^ 32).
-template <int D>
+// Epilogue of a forward workgroup's wave: normalise its 32 rows (wrow0 ..) and
+// write O (bf16) and LSE (natural log), or, for a split-K part, the part's fp32
+// O and LSE.  A row that saw no key (possible for a chunk or a part) gets O = 0
+// and LSE = -inf.  m: the base-2 exponent offset; lsum: this lane's partial row
+// sum (the other half of the row's keys is on lane l ^ 32).  smem: the tile
+// buffers, no longer in use by any wave.
+template <int D, int NW>
 __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const f32x16 (&oacc)[D / 32],
-                                             float m, float lsum, int row, int seg_hi, int h,
-                                             int part, int hh) {
+                                             float m, float lsum, int wrow0, int seg_hi, int h,
+                                             int part, int w, uint16_t* smem) {
+  const int l = __lane_id();
+  const int row = wrow0 + (l & 31);
   const size_t qstride = (size_t)a.hq * D;
   const float ltot = lsum + partner32(lsum);
-  if (row >= seg_hi) return;
   const bool seen = ltot > 0.f;
   const float inv = seen ? 1.f / ltot : 0.f;
   const float lse = seen ? (m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
+  const bool write_lse = l < 32 && row < seg_hi;
   if (a.split.parts > 1) {
-    float* op = a.part_o + ((size_t)part * a.total_tokens + row) * qstride + (size_t)h * D;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = {oacc[db][g * 4 + 0] * inv, oacc[db][g * 4 + 1] * inv,
-                         oacc[db][g * 4 + 2] * inv, oacc[db][g * 4 + 3] * inv};
-        *reinterpret_cast<f32x4*>(op + db * 32 + g * 8 + hh * 4) = v;
-      }
-    if (hh == 0) a.part_lse[((size_t)part * a.hq + h) * a.total_tokens + row] = lse;
+    constexpr int PASS = FwdCfg<D, NW>::F32_PASS;
+    const size_t prow = (size_t)part * a.total_tokens + wrow0;
+    store_rows_f32<D, PASS>(oacc, inv, a.part_o + prow * qstride + (size_t)h * D, qstride,
+                            seg_hi - wrow0, false,
+                            reinterpret_cast<float*>(smem) + w * PASS * kF32Block);
+    if (write_lse) a.part_lse[((size_t)part * a.hq + h) * a.total_tokens + row] = lse;
   } else {
-    uint16_t* op = a.o + (size_t)row * qstride + (size_t)h * D;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x2 v01 = {oacc[db][g * 4 + 0] * inv, oacc[db][g * 4 + 1] * inv};
-        f32x2 v23 = {oacc[db][g * 4 + 2] * inv, oacc[db][g * 4 + 3] * inv};
-        bf16x2 b01 = __builtin_convertvector(v01, bf16x2);
-        bf16x2 b23 = __builtin_convertvector(v23, bf16x2);
-        u32x2 pk = {__builtin_bit_cast(uint32_t, b01), __builtin_bit_cast(uint32_t, b23)};
-        *reinterpret_cast<u32x2*>(op + db * 32 + g * 8 + hh * 4) = pk;
-      }
-    if (hh == 0) a.lse[(size_t)h * a.total_tokens + row] = lse;
+    store_rows_bf16<D>(oacc, inv, a.o + (size_t)wrow0 * qstride + (size_t)h * D, qstride,
+                       seg_hi - wrow0, smem + w * 32 * kBf16Pitch<D>);
+    if (write_lse) a.lse[(size_t)h * a.total_tokens + row] = lse;
   }
 }
 
@@ -387,11 +381,13 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
         issue(tn);
       }
     }
-    // the last tile's empty-range copies land before the workgroup ends
+    // the last tile's empty-range copies have landed and every wave is done
+    // with the tiles before the outputs are turned in their place
     wait_dma();
+    __syncthreads();
   }
 
-  fwd_epilogue<D>(a, oacc, m, lsum, row, seg_hi, h, part, hh);
+  fwd_epilogue<D, NW>(a, oacc, m, lsum, wrow0, seg_hi, h, part, w, smem);
 }
 
 // n floats set to zero, 4 per thread
