@@ -43,8 +43,10 @@
  *     parts (split-K) whose fp32 partial results are combined in a second
  *     kernel: 2 or 4 parts per item, or, for a causal single sequence whose
  *     parts fit one round on the GPU, more parts for the heavier items (at
- *     most 16); the choice depends only on the sizes and the causal flag
- *     (the workspace queries cover both values of the flag).  A segment's results
+ *     most 16), or among the waves of a workgroup; the choice depends only on
+ *     the sizes, the causal flag (the workspace queries cover both values of
+ *     the flag) and, for a chunk pair, its offsets.  A chunk pair in a workspace
+ *     too small for its parts takes fewer.  A segment's results
  *     therefore do not depend on the other segments of its batch, but a batch
  *     and the same segment alone may round differently when one of the two
  *     launches is split.

@@ -122,11 +122,16 @@ struct BwdArgs {
 // the other's matrix products.  Under split-K a workgroup takes one
 // contiguous part of the tile's query steps and writes partial dK/dV for
 // split_sum_kernel.
-template <int D>
+// QG = 2: the waves are two query groups of four; a workgroup covers 128 keys
+// and a wave takes one 32-row half of every step.  The groups' partial dK and dV
+// meet in LDS at the end.  For launches whose 256-key tiles are too few to fill
+// the chip (half as many keys per workgroup, no partial results in memory).
+template <int D, int QG = 1>
 struct DkdvCfg {
   static constexpr int NW = 8;
-  static constexpr int BK = 32 * NW;  // keys per workgroup (32 per wave)
-  static constexpr int BQ = 64;       // query rows per step (two halves of 32)
+  static constexpr int KW = NW / QG;    // waves along the keys
+  static constexpr int BK = 32 * KW;    // keys per workgroup (32 per wave)
+  static constexpr int BQ = 64;         // query rows per step (two halves of 32)
   static constexpr int NT = NW * 64;
   using QL = DualLayout<D>;  // Q and dO: read as rows (S, dP) and transposed (dK, dV)
   using KL = RowsLayout<D>;  // K: read as rows only
@@ -134,7 +139,9 @@ struct DkdvCfg {
   static constexpr int KTILE = KL::elems(BK);
   // per stage: Q tile, dO tile, lse2[BQ], D[BQ]
   static constexpr int STAGE = 2 * QTILE * 2 + 2 * BQ * 4;
-  static constexpr int LDS_BYTES = 2 * STAGE + KTILE * 2;
+  static constexpr int TILE_BYTES = 2 * STAGE + KTILE * 2;
+  static constexpr int OUT_BYTES = NW * (D / 32) * kF32Block * 4;
+  static constexpr int LDS_BYTES = QG > 1 && OUT_BYTES > TILE_BYTES ? OUT_BYTES : TILE_BYTES;
   // 32-column blocks of a gradient turned at a time (store_rows_f32)
   static constexpr int F32_PASS = D / 32;
   static_assert(NW * F32_PASS * kF32Block * 4 <= LDS_BYTES,
@@ -142,9 +149,13 @@ struct DkdvCfg {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
 
-template <int D>
-__global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
-  using C = DkdvCfg<D>;
+// (d = 64: at most 168 registers, 12 wave slots per CU, so that the next
+// workgroup starts while half of the waves of one over a short segment still
+// store: 70 segments of 16-107 tokens x 16 heads 29 -> 25 us, and 21.5 with the
+// waves without keys ending before the stores)
+template <int D, int QG>
+__global__ void __launch_bounds__(512, D == 64 ? 3 : 1) bwd_dkdv_kernel(BwdArgs a) {
+  using C = DkdvCfg<D, QG>;
   using QL = typename C::QL;
   using KL = typename C::KL;
   constexpr int BK = C::BK, BQ = C::BQ, NW = C::NW;
@@ -176,7 +187,9 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
   const int l = __lane_id();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int hh = l >> 5;
-  const int kw0 = k0 + w * 32;    // first key of this wave
+  const int kw = QG == 1 ? w : w % C::KW;  // key block
+  const int qg = QG == 1 ? 0 : w / C::KW;  // query group
+  const int kw0 = k0 + kw * 32;    // first key of this wave
   const int key = kw0 + (l & 31);  // this lane's key
   const size_t qstride = (size_t)a.hq * D;
   const size_t kvstride = (size_t)a.hkv * D;
@@ -275,7 +288,7 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
       constexpr int NKS = D / 16, PIPE = PDY_DKDV_PIPE;
       const uint32_t qa = lds_addr(qs) + (q_row + hf * 32 * QL::ROW) * 2;
       const uint32_t ga = lds_addr(gs) + (q_row + hf * 32 * QL::ROW) * 2;
-      const uint32_t ka = lds_addr(ktile_s) + (k_row + w * 32 * KL::ROW) * 2;
+      const uint32_t ka = lds_addr(ktile_s) + (k_row + kw * 32 * KL::ROW) * 2;
       u32x4 rq[PIPE + 1], rk[PIPE + 1], rg[PIPE + 1];
       auto rd = [&](auto KS) __attribute__((always_inline)) {
         constexpr int ks = decltype(KS)::value, sl = ks % (PIPE + 1);
@@ -403,7 +416,7 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
       const int bn = (step + 1) & 1;
       // every wave has PQ - 1 copies of each tile; a wave's last one may lie
       // past the tile (a branch), so those two go out at the last K-step
-      const bool ran = compute(step, cur, 0, [&](auto KS) __attribute__((always_inline)) {
+      const bool ran = compute(step, cur, QG > 1 ? qg : 0, [&](auto KS) __attribute__((always_inline)) {
         constexpr int c = decltype(KS)::value;
         if constexpr (c < PQ - 1) {
           qd.issue_one(c, rsq, qbuf(bn));
@@ -415,15 +428,17 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
         }
       });
       if (!ran && more) issue(step + 1, nxt);
-      compute(step, cur, 1, [](auto) {});
+      if constexpr (QG == 1) compute(step, cur, 1, [](auto) {});
       cur = nxt;
     }
   }
 
   // every copy this wave issued has landed (a part with no query steps still
   // issued its K copies) and every wave is done with the tiles before the
-  // gradients are turned in their place
+  // gradients are turned in their place; waves without keys end here (a barrier
+  // counts the waves that are left) and free their slots for the next workgroup
   wait_dma();
+  if (kw0 >= k_hi) return;
   __syncthreads();
   {
     const bool split = a.split_kv.parts > 1;
@@ -431,6 +446,31 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
     const size_t poff = (size_t)part * (a.chunked ? a.tk : a.total_tokens) * kvstride + off;
     float* lds = reinterpret_cast<float*>(smem) + w * C::F32_PASS * kF32Block;
     const bool add = a.accumulate && !split;
+    if constexpr (QG == 2) {
+      // the groups exchange halves: group 0 keeps dK and hands over its dV,
+      // group 1 the other way round; each adds the partner's (whose slot it
+      // then turns its sum in)
+      const int lane_off = acc_slot_lane();
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+        acc_to_lds(qg ? dka[db] : dva[db], 1.f, lds + db * kF32Block, lane_off);
+      __syncthreads();
+      lds = reinterpret_cast<float*>(smem) + (w ^ C::KW) * C::F32_PASS * kF32Block;
+      f32x16 sum[D / 32];
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(lds + db * kF32Block + lane_off + g * 8);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            sum[db][g * 4 + e] = (qg ? dva[db] : dka[db])[g * 4 + e] + x[e];
+        }
+      float* dst = qg ? (split ? a.part_dv + poff : a.dv + off)
+                      : (split ? a.part_dk + poff : a.dk + off);
+      store_rows_f32<D, C::F32_PASS>(sum, qg ? 1.f : a.scale, dst, kvstride, k_hi - kw0, add, lds);
+      return;
+    }
     store_rows_f32<D, C::F32_PASS>(dka, a.scale, split ? a.part_dk + poff : a.dk + off, kvstride,
                                    k_hi - kw0, add, lds);
     store_rows_f32<D, C::F32_PASS>(dva, 1.f, split ? a.part_dv + poff : a.dv + off, kvstride,
@@ -438,10 +478,13 @@ __global__ void __launch_bounds__(512) bwd_dkdv_kernel(BwdArgs a) {
   }
 }
 
-template <int D, int NW>
+// KG > 1: key groups, as in the forward (the groups' partial dQ are added).
+template <int D, int NW, int KG = 1>
 struct DqCfg {
-  static constexpr int BQ = 32 * NW;
+  static constexpr int RG = NW / KG;  // row groups
+  static constexpr int BQ = 32 * RG;
   static constexpr int BK = (NW == 8) ? PDY_DQ_BK : 64;  // keys per tile
+  static constexpr int WK = BK / KG;                     // keys of a tile per wave
   static constexpr int NT = NW * 64;
   using KL = DualLayout<D>;  // K is read as rows (S^T) and transposed (dQ^T)
   using VL = RowsLayout<D>;  // V is read as rows (dP^T)
@@ -450,13 +493,13 @@ struct DqCfg {
   static constexpr int LDS_BYTES = 2 * (KTILE + VTILE) * 2;
   // 32-column blocks of dQ turned at a time (store_rows_f32)
   static constexpr int F32_PASS = NW * (D / 32) * kF32Block * 4 <= LDS_BYTES ? D / 32 : 1;
-  static_assert(NW * F32_PASS * kF32Block * 4 <= LDS_BYTES,
+  static_assert(NW * (KG > 1 ? D / 32 : F32_PASS) * kF32Block * 4 <= LDS_BYTES,
                 "dQ is turned in the tile buffers");
 };
 
-template <int D, int NW>
+template <int D, int NW, int KG>
 __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArgs a) {
-  using C = DqCfg<D, NW>;
+  using C = DqCfg<D, NW, KG>;
   using KL = typename C::KL;
   using VL = typename C::VL;
   constexpr int BQ = C::BQ, BK = C::BK;
@@ -482,8 +525,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
   const int l = __lane_id();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int hh = l >> 5;
-  const int row = q0 + w * 32 + (l & 31);
-  const int wrow0 = q0 + w * 32;
+  const int rg = KG == 1 ? w : w % C::RG;  // row group
+  const int kg = KG == 1 ? 0 : w / C::RG;  // key group
+  const int wrow0 = q0 + rg * 32;
+  const int row = wrow0 + (l & 31);
+  const int wk0 = kg * C::WK;  // first key of a tile this wave takes
   const int wrow_last = wrow0 + 31;
   const int key_lim = a.causal ? min(row + shift, k_hi - 1) : k_hi - 1;
   const size_t qstride = (size_t)a.hq * D;
@@ -513,7 +559,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
       // a row without any visible key has LSE = -inf and no gradient
       if (lse2 == -INFINITY) lse2 = INFINITY;
       // D of the row for the dK/dV kernel, which runs after this one
-      if (hh == 0 && part == 0) a.dd[(size_t)h * a.total_tokens + row] = ddv;
+      if (hh == 0 && part == 0 && kg == 0) a.dd[(size_t)h * a.total_tokens + row] = ddv;
     }
   }
   f32x16 dqa[D / 32];
@@ -539,15 +585,16 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
   // after the products of the N-th K-step of S^T/dP^T, counted over the
   // tile's 32-key blocks (active waves only)
   auto compute = [&](int it, auto&& hook) __attribute__((always_inline)) {
-    const int k0 = k_lo + it * BK;
-    const bool active = (wrow0 < seg_hi) && (!a.causal || k0 <= wrow_last + shift);
+    const int k0 = k_lo + it * BK + wk0;
+    const bool active = (wrow0 < seg_hi) && (KG == 1 || k0 < kv_end) &&
+                        (!a.causal || k0 <= wrow_last + shift);
     if (!active) return false;
-    const uint32_t kra = lds_addr(kbuf(it)) + k_row * 2;
-    const uint32_t ka = lds_addr(kbuf(it)) + k_tr * 2;
-    const uint32_t vra = lds_addr(vbuf(it)) + v_row * 2;
-    const bool need_mask = (a.causal && k0 + BK - 1 > wrow0 + shift) || (k0 + BK > k_hi);
+    const uint32_t kra = lds_addr(kbuf(it)) + (k_row + wk0 * KL::ROW) * 2;
+    const uint32_t ka = lds_addr(kbuf(it)) + (k_tr + wk0 * KL::ROW) * 2;
+    const uint32_t vra = lds_addr(vbuf(it)) + (v_row + wk0 * VL::ROW) * 2;
+    const bool need_mask = (a.causal && k0 + C::WK - 1 > wrow0 + shift) || (k0 + C::WK > k_hi);
     // one 32-key block at a time keeps S^T and dP^T to 32 registers
-    static_for<BK / 32>([&](auto KB) {
+    static_for<C::WK / 32>([&](auto KB) {
       constexpr int kb = decltype(KB)::value;
       // S^T and dP^T; the K and V fragments are read PIPE K-steps ahead
       f32x16 s = zero16(), dp = zero16();
@@ -616,8 +663,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
     // the next tile's copies go out one every GAP K-steps of S^T/dP^T rather
     // than all at once after the barrier, as in the dK/dV kernel
     constexpr int PK = KD::PER_WAVE, NCOPY = PK + VD::PER_WAVE;
-    constexpr int GAP = (BK / 32) * (D / 16) / NCOPY;
-    static_assert(GAP >= 1, "one copy per K-step at most");
+    constexpr int STEPS = (C::WK / 32) * (D / 16);  // K-steps of a tile
+    constexpr int GAP = STEPS / NCOPY > 1 ? STEPS / NCOPY : 1;
     KD kd;
     VD vd;
     kd.init(kvstride);
@@ -644,24 +691,58 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
       const int bn = (it + 1) & 1;
       const bool ran = compute(it, [&](auto N) __attribute__((always_inline)) {
         constexpr int n = decltype(N)::value;
-        if constexpr (n % GAP == 0 && n / GAP < PK) {
-          kd.issue_one(n / GAP, rsk, kbuf(bn));
-        } else if constexpr (n % GAP == 0 && n / GAP < NCOPY - 1) {
-          vd.issue_one(n / GAP - PK, rsv, vbuf(bn));
-        } else if constexpr (n == (BK / 32) * (D / 16) - 1) {
-          vd.issue_one(NCOPY - 1 - PK, rsv, vbuf(bn));
-        }
+        auto copy = [&](auto CI) __attribute__((always_inline)) {
+          constexpr int c = decltype(CI)::value;
+          if constexpr (c < PK) kd.issue_one(c, rsk, kbuf(bn));
+          else vd.issue_one(c - PK, rsv, vbuf(bn));
+        };
+        if constexpr (n % GAP == 0 && n / GAP < NCOPY - 1)
+          copy(std::integral_constant<int, n / GAP>{});
+        // the last copy, and those beyond the tile's K-steps
+        if constexpr (n == STEPS - 1)
+          static_for<NCOPY>([&](auto CI) {
+            if constexpr (decltype(CI)::value * GAP >= STEPS || decltype(CI)::value == NCOPY - 1)
+              copy(CI);
+          });
       });
       if (!ran && more) issue(it + 1);
     }
     // the last tile's empty-range copies have landed and every wave is done
-    // with the tiles before dQ is turned in their place
+    // with the tiles before dQ is turned in their place; waves without rows end
+    // here, as in the forward
     wait_dma();
+    if (wrow0 >= seg_hi) return;
     __syncthreads();
   }
 
   const bool split = a.split_q.parts > 1;
   const size_t off = (size_t)wrow0 * qstride + (size_t)h * D;
+  if constexpr (KG > 1) {
+    float* slots = reinterpret_cast<float*>(smem) + rg * KG * (D / 32) * kF32Block;
+    const int lane_off = acc_slot_lane();
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+      acc_to_lds(dqa[db], a.scale, slots + (kg * (D / 32) + db) * kF32Block, lane_off);
+    __syncthreads();
+    float* dst = split ? a.part_dq + (size_t)part * a.total_tokens * qstride + off : a.dq + off;
+    combine_groups<D, KG>(
+        slots, kg,
+        [](int, float (&wt)[KG]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int j = 0; j < KG; ++j) wt[j] = 1.f;
+        },
+        [&](int r, int c, const float (&x)[8]) __attribute__((always_inline)) {
+          if (wrow0 + r >= seg_hi) return;
+          float* to = dst + (size_t)r * qstride + c;
+#pragma unroll
+          for (int e = 0; e < 8; e += 4) {
+            f32x4 v = {x[e], x[e + 1], x[e + 2], x[e + 3]};
+            if (a.accumulate && !split) v += *reinterpret_cast<const f32x4*>(to + e);
+            *reinterpret_cast<f32x4*>(to + e) = v;
+          }
+        });
+    return;
+  }
   store_rows_f32<D, C::F32_PASS>(
       dqa, a.scale, split ? a.part_dq + (size_t)part * a.total_tokens * qstride + off : a.dq + off,
       qstride, seg_hi - wrow0, a.accumulate && !split,

@@ -230,16 +230,16 @@ __device__ __forceinline__ void row_issue(uint32_t lane_addr, u32x4& r) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(lane_addr), "i"(off));
 }
 template <int N>
+__device__ __forceinline__ void row_wait(u32x4& a) {
+  asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "i"(N));
+}
+template <int N>
 __device__ __forceinline__ void row_wait(u32x4& a, u32x4& b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "i"(N));
 }
 template <int N>
 __device__ __forceinline__ void row_wait(u32x4& a, u32x4& b, u32x4& c) {
   asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a), "+v"(b), "+v"(c) : "i"(N));
-}
-template <int N>
-__device__ __forceinline__ void row_wait(u32x4& a, u32x4& b, u32x4& c, u32x4& d) {
-  asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "i"(N));
 }
 __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& r) { return __builtin_bit_cast(bf16x8, r); }
 
@@ -352,10 +352,10 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
   asm volatile("" ::: "memory");
 }
-// Four 16-byte LDS reads STEP bytes apart, waited for.
-template <int OFF, int STEP>
+// Four 16-byte LDS reads at byte offsets O0..O3 from addr, waited for.
+template <int O0, int O1, int O2, int O3>
 __device__ __forceinline__ void lds_read4(uint32_t addr, u32x4 (&v)[4]) {
-  static_assert(OFF + 3 * STEP < 65536, "LDS offset out of range");
+  static_assert(O0 < 65536 && O1 < 65536 && O2 < 65536 && O3 < 65536, "LDS offset out of range");
   asm volatile(
       "ds_read_b128 %0, %4 offset:%5\n\t"
       "ds_read_b128 %1, %4 offset:%6\n\t"
@@ -363,47 +363,57 @@ __device__ __forceinline__ void lds_read4(uint32_t addr, u32x4 (&v)[4]) {
       "ds_read_b128 %3, %4 offset:%8\n\t"
       "s_waitcnt lgkmcnt(0)"
       : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-      : "v"(addr), "i"(OFF), "i"(OFF + STEP), "i"(OFF + 2 * STEP), "i"(OFF + 3 * STEP)
+      : "v"(addr), "i"(O0), "i"(O1), "i"(O2), "i"(O3)
       : "memory");
+}
+
+// A wave's accumulator tile into its LDS slot: 32 rows of D floats in 32-column
+// blocks of kF32Pitch floats a row (rows 16 bytes apart in the banks:
+// conflict-free written by rows of accumulators and read by rows of columns).
+constexpr int kF32Pitch = 36;
+constexpr int kF32Block = 32 * kF32Pitch;
+__device__ __forceinline__ int acc_slot_lane() {
+  const int l = __lane_id();
+  return (l & 31) * kF32Pitch + (l >> 5) * 4;
+}
+__device__ __forceinline__ void acc_to_lds(const f32x16& x, float mul, float* block, int lane_off) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    *reinterpret_cast<f32x4*>(block + lane_off + g * 8) =
+        f32x4{x[g * 4] * mul, x[g * 4 + 1] * mul, x[g * 4 + 2] * mul, x[g * 4 + 3] * mul};
 }
 
 // One wave's 32 rows of D floats, acc * mul (mul: this lane's row's factor), to
 // dst (row 0, column 0; `stride` floats from row to row), rows < nrows only;
-// accumulate: added to what dst holds.  A 32-column block takes kF32Pitch floats
-// a row in LDS (rows 16 bytes apart in the banks: conflict-free both ways).
-// PASS blocks are turned at a time: PASS * kF32Block floats of LDS per wave.
-constexpr int kF32Pitch = 36;
-constexpr int kF32Block = 32 * kF32Pitch;
+// accumulate: added to what dst holds.  PASS blocks are turned at a time:
+// PASS * kF32Block floats of LDS per wave.
 template <int D, int PASS>
 __device__ __forceinline__ void store_rows_f32(const f32x16 (&acc)[D / 32], float mul, float* dst,
                                                size_t stride, int nrows, bool accumulate,
                                                float* lds) {
   static_assert((D / 32) % PASS == 0, "whole passes");
+  if (nrows <= 0) return;  // wave-uniform
   const int l = __lane_id();
-  const int wr = (l & 31) * kF32Pitch + (l >> 5) * 4;  // write: this lane's row
-  const int rr = l >> 3, c = (l & 7) * 4;              // read: 8 lanes a row
+  const int wr = acc_slot_lane();
+  const int rr = l >> 3, c = (l & 7) * 4;  // read: 8 lanes a row
   const uint32_t rd = lds_addr(lds) + (rr * kF32Pitch + c) * 4;
+  // (one address per lane, then uniform steps of 8 rows)
+  float* const mine = dst + (size_t)rr * stride + c;
   static_for<D / 32 / PASS>([&](auto Pass) {
     constexpr int p = decltype(Pass)::value * PASS;
 #pragma unroll
-    for (int b = 0; b < PASS; ++b)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x16& x = acc[p + b];
-        *reinterpret_cast<f32x4*>(lds + b * kF32Block + wr + g * 8) =
-            f32x4{x[g * 4] * mul, x[g * 4 + 1] * mul, x[g * 4 + 2] * mul, x[g * 4 + 3] * mul};
-      }
+    for (int b = 0; b < PASS; ++b) acc_to_lds(acc[p + b], mul, lds + b * kF32Block, wr);
     wave_lds_fence();
     static_for<PASS>([&](auto B) {
       constexpr int b = decltype(B)::value;
       u32x4 raw[4];
-      lds_read4<b * kF32Block * 4, 8 * kF32Pitch * 4>(rd, raw);
+      constexpr int o = b * kF32Block * 4, st = 8 * kF32Pitch * 4;
+      lds_read4<o, o + st, o + 2 * st, o + 3 * st>(rd, raw);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int r = i * 8 + rr;
         f32x4 v = __builtin_bit_cast(f32x4, raw[i]);
-        float* to = dst + (size_t)r * stride + (p + b) * 32 + c;
-        if (r < nrows) {
+        float* to = mine + (size_t)i * 8 * stride + (p + b) * 32;
+        if (i * 8 + rr < nrows) {
           if (accumulate) v += *reinterpret_cast<const f32x4*>(to);
           *reinterpret_cast<f32x4*>(to) = v;
         }
@@ -421,6 +431,7 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[D / 32], flo
                                                 uint16_t* dst, size_t stride, int nrows,
                                                 uint16_t* lds) {
   constexpr int P = kBf16Pitch<D>, LANES = D / 8, ROWS = 64 / LANES;
+  if (nrows <= 0) return;  // wave-uniform
   const int l = __lane_id();
   const int wr = (l & 31) * P + (l >> 5) * 4;
 #pragma unroll
@@ -437,15 +448,47 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[D / 32], flo
   wave_lds_fence();
   const int rr = l / LANES, c = (l % LANES) * 8;
   const uint32_t rd = lds_addr(lds) + (rr * P + c) * 2;
+  uint16_t* const mine = dst + (size_t)rr * stride + c;
   static_for<32 / ROWS / 4>([&](auto I) {
     constexpr int i0 = decltype(I)::value * 4;
     u32x4 v[4];
-    lds_read4<i0 * ROWS * P * 2, ROWS * P * 2>(rd, v);
+    constexpr int o = i0 * ROWS * P * 2, st = ROWS * P * 2;
+    lds_read4<o, o + st, o + 2 * st, o + 3 * st>(rd, v);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int r = (i0 + i) * ROWS + rr;
-      if (r < nrows) *reinterpret_cast<u32x4*>(dst + (size_t)r * stride + c) = v[i];
+      if ((i0 + i) * ROWS + rr < nrows)
+        *reinterpret_cast<u32x4*>(mine + (size_t)(i0 + i) * ROWS * stride) = v[i];
     }
+  });
+}
+
+// Key groups: the KG waves of a row group hold partial sums of the same 32 rows
+// over different keys, all in LDS slots of D / 32 blocks (slot rg * KG + kg of
+// row group rg, at `slot`).  Wave kg combines the rows [kg, kg + 1) * 32 / KG, 8
+// consecutive columns of a row per lane: weights(row, w) sets the groups'
+// weights, then out(row, column, x) gets x = sum_j w[j] * partial j.
+template <int D, int KG, class W, class F>
+__device__ __forceinline__ void combine_groups(const float* slot, int kg, W&& weights, F&& out) {
+  constexpr int LANES = D / 8, ROWS = 64 / LANES, SLOT = D / 32 * kF32Block * 4;
+  const int l = __lane_id();
+  const int c = (l % LANES) * 8;
+  static_for<32 / KG / ROWS>([&](auto I) {
+    const int r = kg * (32 / KG) + decltype(I)::value * ROWS + l / LANES;
+    const uint32_t addr =
+        lds_addr(slot) + ((c >> 5) * kF32Block + r * kF32Pitch + (c & 31)) * 4;
+    float w[KG];
+    weights(r, w);
+    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    static_for<KG / 2>([&](auto J) {
+      constexpr int j = decltype(J)::value * 2, o = j * SLOT;
+      u32x4 raw[4];
+      lds_read4<o, o + 16, o + SLOT, o + SLOT + 16>(addr, raw);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        x[e] += w[j] * __uint_as_float(raw[e >> 2][e & 3]) +
+                w[j + 1] * __uint_as_float(raw[2 + (e >> 2)][e & 3]);
+    });
+    out(r, c, x);
   });
 }
 

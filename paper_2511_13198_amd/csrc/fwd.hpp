@@ -39,25 +39,35 @@ constexpr float kRescaleSlack = 8.0f;
 #define PDY_FWD_STAGES 2
 #endif
 
-template <int D, int NW>
+// KG > 1: key groups.  The workgroup's waves are KG groups that take 1 / KG of
+// every key tile each, over the same NW / KG * 32 query rows, and combine their
+// partial O at the end through LDS.  Query tiles get smaller (more workgroups,
+// shorter chains of tiles) with no partial results in memory; each K/V tile
+// is then copied for fewer rows.
+template <int D, int NW, int KG = 1>
 struct FwdCfg {
-  static constexpr int BQ = 32 * NW;
+  static constexpr int RG = NW / KG;  // row groups
+  static constexpr int BQ = 32 * RG;
   // keys per tile (one barrier); 4-wave workgroups keep 64 so that two of
   // them fit a CU's LDS
-  static constexpr int BK = (D == 128 && NW == 8) ? PDY_FWD_BK : 64;
-  static constexpr int BKS = 64;                            // keys per softmax step
+  static constexpr int BK = KG > 1 ? 128 : (D == 128 && NW == 8) ? PDY_FWD_BK : 64;
+  static constexpr int WK = BK / KG;               // keys of a tile per wave
+  static constexpr int BKS = WK < 64 ? WK : 64;    // keys per softmax step
   static constexpr int NT = NW * 64;
   using KL = RowsLayout<D>;  // K is only read as rows
   using VL = DualLayout<D>;  // V is only read transposed
   static constexpr int KTILE = KL::elems(BK);
   static constexpr int VTILE = VL::elems(BK);
   // K/V tiles in flight: the direct copies run STAGES-1 tiles ahead
-  static constexpr int STAGES = PDY_FWD_STAGES;
+  static constexpr int STAGES = KG > 1 && D == 64 ? 4 : PDY_FWD_STAGES;
   static constexpr int LDS_BYTES = STAGES * (KTILE + VTILE) * 2;
   // 32-column blocks of the fp32 partial O turned at a time (store_rows_f32)
   static constexpr int F32_PASS = D == 128 ? 4 : 1;
-  static_assert(NW * F32_PASS * kF32Block * 4 <= LDS_BYTES &&
-                    NW * 32 * kBf16Pitch<D> * 2 <= LDS_BYTES,
+  // byte offset of the groups' row statistics behind their partial O
+  static constexpr int STAT_OFF = NW * (D / 32) * kF32Block * 4;
+  static_assert(KG == 1 ? NW * F32_PASS * kF32Block * 4 <= LDS_BYTES &&
+                              NW * 32 * kBf16Pitch<D> * 2 <= LDS_BYTES
+                        : STAT_OFF + NW * 32 * 8 <= LDS_BYTES,
                 "the output tile is turned in the tile buffers");
 };
 
@@ -126,9 +136,70 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const f32x16 (&oa
   }
 }
 
-template <int D, int NW>
+// The same for key groups: the groups' partial O (unnormalised) and their m and
+// row sums meet in LDS, weighted 2^(m_j - max_j m_j).
+template <int D, int NW, int KG>
+__device__ __forceinline__ void fwd_epilogue_groups(const FwdArgs& a, const f32x16 (&oacc)[D / 32],
+                                                    float m, float lsum, int wrow0, int seg_hi,
+                                                    int h, int part, int rg, int kg,
+                                                    uint16_t* smem) {
+  using C = FwdCfg<D, NW, KG>;
+  const size_t qstride = (size_t)a.hq * D;
+  const int l = __lane_id();
+  float* slots = reinterpret_cast<float*>(smem) + rg * KG * (D / 32) * kF32Block;
+  f32x2* stat = reinterpret_cast<f32x2*>(reinterpret_cast<uint8_t*>(smem) + C::STAT_OFF) +
+                rg * KG * 32;
+  const float ltot = lsum + partner32(lsum);
+  const int lane_off = acc_slot_lane();
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+    acc_to_lds(oacc[db], 1.f, slots + (kg * (D / 32) + db) * kF32Block, lane_off);
+  if (l < 32) stat[kg * 32 + l] = f32x2{m, ltot};
+  __syncthreads();
+  float lse = 0.f;  // of the row at hand
+  combine_groups<D, KG>(
+      slots, kg,
+      [&](int r, float (&w)[KG]) __attribute__((always_inline)) {
+        f32x2 st[KG];
+        float mx = -INFINITY, tot = 0.f;
+#pragma unroll
+        for (int j = 0; j < KG; ++j) {
+          st[j] = stat[j * 32 + r];
+          mx = fmaxf(mx, st[j][0]);
+        }
+#pragma unroll
+        for (int j = 0; j < KG; ++j) {
+          w[j] = st[j][1] > 0.f ? fast_exp2(st[j][0] - mx) : 0.f;
+          tot += w[j] * st[j][1];
+        }
+        const float inv = tot > 0.f ? 1.f / tot : 0.f;
+#pragma unroll
+        for (int j = 0; j < KG; ++j) w[j] *= inv;
+        lse = tot > 0.f ? (mx + __builtin_log2f(tot)) * kLn2 : -INFINITY;
+      },
+      [&](int r, int c, const float (&x)[8]) __attribute__((always_inline)) {
+        const int row = wrow0 + r;
+        if (row >= seg_hi) return;
+        if (a.split.parts > 1) {
+          float* to = a.part_o + ((size_t)part * a.total_tokens + row) * qstride + (size_t)h * D + c;
+          *reinterpret_cast<f32x4*>(to) = f32x4{x[0], x[1], x[2], x[3]};
+          *reinterpret_cast<f32x4*>(to + 4) = f32x4{x[4], x[5], x[6], x[7]};
+          if (c == 0) a.part_lse[((size_t)part * a.hq + h) * a.total_tokens + row] = lse;
+        } else {
+          u32x4 v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            v[i] = __builtin_bit_cast(
+                uint32_t, __builtin_convertvector(f32x2{x[2 * i], x[2 * i + 1]}, bf16x2));
+          *reinterpret_cast<u32x4*>(a.o + (size_t)row * qstride + (size_t)h * D + c) = v;
+          if (c == 0) a.lse[(size_t)h * a.total_tokens + row] = lse;
+        }
+      });
+}
+
+template <int D, int NW, int KG>
 __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a) {
-  using C = FwdCfg<D, NW>;
+  using C = FwdCfg<D, NW, KG>;
   using KL = typename C::KL;
   using VL = typename C::VL;
   constexpr int BQ = C::BQ, BK = C::BK, BKS = C::BKS;
@@ -156,8 +227,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
   const int l = __lane_id();
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int hh = l >> 5;
-  const int row = q0 + w * 32 + (l & 31);  // this lane's query row
-  const int wrow0 = q0 + w * 32;
+  const int rg = KG == 1 ? w : w % C::RG;  // row group
+  const int kg = KG == 1 ? 0 : w / C::RG;  // key group
+  const int wrow0 = q0 + rg * 32;
+  const int row = wrow0 + (l & 31);  // this lane's query row
+  const int wk0 = kg * C::WK;        // first key of a tile this wave takes
   const int wrow_last = wrow0 + 31;
   // last key this row may see
   const int key_lim = a.causal ? min(row + shift, k_hi - 1) : k_hi - 1;
@@ -194,7 +268,9 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
   const int k_lane = row_lane_base<KL>();
   const int v_lane = tr_lane_base<VL>();
   auto active = [&](int t) __attribute__((always_inline)) {
-    return (wrow0 < seg_hi) && (!a.causal || k_lo + t * BK <= wrow_last + shift);
+    const int k0 = k_lo + t * BK + wk0;
+    return (wrow0 < seg_hi) && (KG == 1 || k0 < kv_end) &&
+           (!a.causal || k0 <= wrow_last + shift);
   };
 
   // S^T for the tile's 32-key blocks; the independent chains interleave
@@ -202,8 +278,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
   // ahead of the products that consume them
   auto compute_s = [&](const uint16_t* ktile, auto&& hook) __attribute__((always_inline)) {
     constexpr int NKS = D / 16, NKB = BKS / 32;
-    static_assert(NKB == 2 || NKB == 4, "two or four 32-key blocks per tile");
-    constexpr int PIPE = NKB == 2 ? 3 : 1;  // lgkmcnt counts at most 15 reads
+    static_assert(NKB == 1 || NKB == 2, "one or two 32-key blocks per step");
+    constexpr int PIPE = 3;
     const uint32_t ka = lds_addr(ktile) + k_lane * 2;
     u32x4 kr[PIPE + 1][NKB];
 #pragma unroll
@@ -216,8 +292,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
     };
     auto wt = [&](auto KS, auto N) __attribute__((always_inline)) {
       constexpr int sl = decltype(KS)::value % (PIPE + 1);
-      if constexpr (NKB == 2) row_wait<decltype(N)::value>(kr[sl][0], kr[sl][1]);
-      else row_wait<decltype(N)::value>(kr[sl][0], kr[sl][1], kr[sl][2], kr[sl][3]);
+      if constexpr (NKB == 1) row_wait<decltype(N)::value>(kr[sl][0]);
+      else row_wait<decltype(N)::value>(kr[sl][0], kr[sl][1]);
     };
     static_for<PIPE>([&](auto KS) { rd(KS); });
     static_for<NKS>([&](auto KS) {
@@ -355,11 +431,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
         };
         // the tile is taken in softmax steps of BKS keys; the first step
         // issues the copies
-        static_for<BK / BKS>([&](auto SUB) {
+        static_for<C::WK / BKS>([&](auto SUB) {
           constexpr int sub = decltype(SUB)::value;
-          const int k0s = k_lo + it * BK + sub * BKS;
+          const int k0s = k_lo + it * BK + wk0 + sub * BKS;
           if (sub == 0 || (k0s < kv_end && (!a.causal || k0s <= wrow_last + shift))) {
-            compute_s(kbuf(it) + sub * BKS * KL::ROW, [&](auto KS) __attribute__((always_inline)) {
+            compute_s(kbuf(it) + (wk0 + sub * BKS) * KL::ROW, [&](auto KS) __attribute__((always_inline)) {
               if constexpr (sub == 0) {
                 constexpr int ks = decltype(KS)::value;
                 if constexpr (ks < PK + PV - 1) copy(KS);
@@ -371,7 +447,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
                   });
               }
             });
-            softmax_pv(k0s, vbuf(it) + sub * BKS * VL::ROW);
+            softmax_pv(k0s, vbuf(it) + (wk0 + sub * BKS) * VL::ROW);
           }
         });
         // a wave's last K copy (which may lie past the tile: a branch) at
@@ -382,12 +458,18 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
       }
     }
     // the last tile's empty-range copies have landed and every wave is done
-    // with the tiles before the outputs are turned in their place
+    // with the tiles before the outputs are turned in their place; waves without
+    // rows end here (a barrier counts the waves that are left) and free their
+    // slots for the next workgroup
     wait_dma();
+    if (wrow0 >= seg_hi) return;
     __syncthreads();
   }
 
-  fwd_epilogue<D, NW>(a, oacc, m, lsum, wrow0, seg_hi, h, part, w, smem);
+  if constexpr (KG == 1)
+    fwd_epilogue<D, NW>(a, oacc, m, lsum, wrow0, seg_hi, h, part, w, smem);
+  else
+    fwd_epilogue_groups<D, NW, KG>(a, oacc, m, lsum, wrow0, seg_hi, h, part, rg, kg, smem);
 }
 
 // n floats set to zero, 4 per thread

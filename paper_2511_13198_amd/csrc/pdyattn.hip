@@ -33,8 +33,6 @@ pdy_status hip_fail(hipError_t e, const char* what) {
 }
 
 constexpr int kTile = 128;  // smallest tile of any kernel (bounds the work items)
-constexpr int kKvTile = pdy::DkdvCfg<128>::BK;  // keys per dK/dV work item
-static_assert(pdy::DkdvCfg<64>::BK == kKvTile, "one key-tile schedule for both head dims");
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -58,6 +56,15 @@ int tiles_of(const Sizes& s, int tile) {
 #endif
 constexpr int64_t kShortSeg = 2048;
 int fwd_waves(const Sizes& s) { return s.maxlen > kShortSeg ? PDY_WAVES_LONG : 4; }
+
+// How a launch's workgroups are made up: forward and dQ by nw waves in `groups`
+// key groups (32 * nw / groups query rows each), dK/dV by 8 waves in `groups`
+// query groups (256 / groups keys each).
+struct Shape {
+  int nw;
+  int groups;
+  int tile() const { return 32 * nw / groups; }
+};
 
 pdy_status check_sizes(int32_t T, int32_t N, int32_t maxlen, int32_t hq, int32_t hkv, int32_t d,
                        Sizes* out) {
@@ -193,16 +200,15 @@ int split_parts(int64_t items, int64_t inner, double tile_us, double part_bytes)
   return p;
 }
 
-int fwd_key_tile(const Sizes& s) {
-  const bool w8 = fwd_waves(s) == 8;
-  if (s.d == 64) return w8 ? pdy::FwdCfg<64, 8>::BK : pdy::FwdCfg<64, 4>::BK;
-  return w8 ? pdy::FwdCfg<128, 8>::BK : pdy::FwdCfg<128, 4>::BK;
+int fwd_key_tile(const Sizes& s, const Shape& sh) {
+  if (sh.groups > 1) return pdy::FwdCfg<128, 8, 2>::BK;
+  if (s.d == 64) return sh.nw == 8 ? pdy::FwdCfg<64, 8>::BK : pdy::FwdCfg<64, 4>::BK;
+  return sh.nw == 8 ? pdy::FwdCfg<128, 8>::BK : pdy::FwdCfg<128, 4>::BK;
 }
 
-int dq_key_tile(const Sizes& s) {
-  const bool w8 = fwd_waves(s) == 8;
-  if (s.d == 64) return w8 ? pdy::DqCfg<64, 8>::BK : pdy::DqCfg<64, 4>::BK;
-  return w8 ? pdy::DqCfg<128, 8>::BK : pdy::DqCfg<128, 4>::BK;
+int dq_key_tile(const Sizes& s, const Shape& sh) {
+  if (s.d == 64) return sh.nw == 8 ? pdy::DqCfg<64, 8>::BK : pdy::DqCfg<64, 4>::BK;
+  return sh.nw == 8 ? pdy::DqCfg<128, 8>::BK : pdy::DqCfg<128, 4>::BK;
 }
 
 // microseconds for one CU to process `pairs` (query, key) pairs of one head
@@ -294,64 +300,191 @@ pdy::Split halve_split(pdy::Split sp) {
   return sp.parts > 1 ? sp : uniform_split(1);
 }
 
-// shape of a query-tile launch (forward, dQ) over a single segment
-pdy::Split q_shape(const Sizes& s, int causal, int rows, int keys) {
-  pdy::Split sp = uniform_split(1);
-  sp.kind = 0;
-  sp.nitems = tiles_of(s, rows);
-  sp.total = (int)s.T;
-  sp.causal = causal;
-  sp.rows = rows;
-  sp.keys = keys;
-  return sp;
+// A launch: its workgroups' shape and its split.
+struct Launch {
+  Shape sh;
+  pdy::Split split;
+};
+
+// What the choice of a launch looks at: rows of queries over rows of keys, sq
+// and sk (one chunk each, `shift` apart, for a context-parallel pair; the same
+// segments otherwise).
+struct Job {
+  const Sizes &sq, &sk;
+  int causal;
+  bool chunk;
+  int shift;
+};
+
+enum Which { FWD, DQ, DKDV };
+
+// One key group (query group) per workgroup: the shape of every launch that
+// fills the chip.
+Shape base_shape(Which k, const Sizes& sq) {
+  return {k == DKDV ? pdy::DkdvCfg<128>::NW : fwd_waves(sq), 1};
 }
 
-// The split of a launch: none for context-parallel pairs (`chunk`), balanced
-// for causal single segments, else uniform.
-pdy::Split choose_split(int p, const Sizes& s, int causal, bool chunk, pdy::Split shape,
-                        int64_t heads, double unit_us, double slice_bytes) {
+// A launch's work in one shape: items per head, the heaviest item's units of
+// inner work, the estimated time of a unit, the bytes of a partial slice.
+struct Work {
+  pdy::Split shape;  // for a balanced split
+  int64_t items, heads, inner;
+  double unit_us, slice;
+};
+Work work_of(Which k, const Job& j, const Shape& sh) {
+  Work w;
+  const int tile = sh.tile();
+  w.shape = uniform_split(1);
+  w.shape.causal = j.causal;
+  if (k == DKDV) {
+    // the heaviest key tile visits every 64-row query step of every head of
+    // its group
+    const int rows = pdy::DkdvCfg<128>::BQ, g = (int)(j.sq.hq / j.sq.hkv);
+    w.items = grid_items(j.sk, tile);
+    w.heads = j.sk.hkv;
+    w.inner = (int64_t)tiles_of(j.sq, rows) * g;
+    w.unit_us = tile_us((double)rows * tile, j.sq, 8.0, 4.5);
+    w.slice = 2.0 * j.sk.T * j.sk.hkv * j.sk.d * 4;
+    w.shape.kind = 1;
+    w.shape.nitems = tiles_of(j.sk, tile);
+    w.shape.total = (int)j.sk.T;
+    w.shape.rows = rows;
+    w.shape.keys = tile;
+    w.shape.group = g;
+  } else {
+    const int keys = k == FWD ? fwd_key_tile(j.sq, sh) : dq_key_tile(j.sq, sh);
+    w.items = grid_items(j.sq, tile);
+    w.heads = j.sq.hq;
+    w.inner = tiles_of(j.sk, keys);
+    w.unit_us = k == FWD ? tile_us((double)tile * keys, j.sq, 4.0, 4.5)
+                         : tile_us((double)tile * keys, j.sq, 6.0, 5.0);
+    w.slice = (double)j.sq.T * j.sq.hq * j.sq.d * 4;
+    w.shape.kind = 0;
+    w.shape.nitems = tiles_of(j.sq, tile);
+    w.shape.total = (int)j.sq.T;
+    w.shape.rows = tile;
+    w.shape.keys = keys;
+  }
+  return w;
+}
+
+// p parts per item, balanced for causal single segments.
+pdy::Split split_of(const Work& w, const Job& j, int p) {
   // (a split launch has fewer than 512 items, so a slice holds far fewer than
   // the 2^31 floats the combine kernels index with 32 bits; kept as a guard)
-  if (p <= 1 || chunk || slice_bytes / 4 >= 2147483648.0) return uniform_split(1);
-  if (s.N == 1 && causal) return balanced_split(shape, p, heads, unit_us, slice_bytes);
+  if (j.sk.T == 0 || w.slice / 4 >= 2147483648.0) return uniform_split(1);
+  if (j.sq.N == 1 && j.causal && !j.chunk)
+    return balanced_split(w.shape, p, w.heads, w.unit_us, w.slice);
   return uniform_split(p);
 }
 
-// sq: the query rows' sizes; sk: the keys' (the same for self-attention
-// over cu's segments, one chunk each for a context-parallel pair)
-pdy::Split fwd_split(const Sizes& sq, const Sizes& sk, int causal, bool chunk) {
-  const int rows = 32 * fwd_waves(sq), keys = fwd_key_tile(sq);
-  const double unit = tile_us((double)rows * keys, sq, 4.0, 4.5);
-  const double slice = (double)sq.T * sq.hq * sq.d * 4;
-  const int p = split_parts(grid_items(sq, rows) * sq.hq, tiles_of(sk, keys), unit, slice);
-  return choose_split(p, sq, causal, chunk, q_shape(sq, causal, rows, keys), sq.hq, unit, slice);
+// The launch in the base shape: no split for a context-parallel pair.
+Launch base_launch(Which k, const Job& j) {
+  const Shape sh = base_shape(k, j.sq);
+  const Work w = work_of(k, j, sh);
+  const int p = split_parts(w.items * w.heads, w.inner, w.unit_us, w.slice);
+  return {sh, p <= 1 || j.chunk ? uniform_split(1) : split_of(w, j, p)};
 }
 
-pdy::Split dq_split(const Sizes& sq, const Sizes& sk, int causal, bool chunk) {
-  const int rows = 32 * fwd_waves(sq), keys = dq_key_tile(sq);
-  const double unit = tile_us((double)rows * keys, sq, 6.0, 5.0);
-  const double slice = (double)sq.T * sq.hq * sq.d * 4;
-  const int p = split_parts(grid_items(sq, rows) * sq.hq, tiles_of(sk, keys), unit, slice);
-  return choose_split(p, sq, causal, chunk, q_shape(sq, causal, rows, keys), sq.hq, unit, slice);
+// Estimated time of an unsplit launch over one segment or chunk pair, by
+// which its number of groups is chosen.  A unit is a workgroup's time on 128
+// keys (forward, dQ) or 64 rows (dK/dV), as measured at d = 128 on a chip that
+// is about full; with 1, 2 and 4 groups a unit covers 256, 128 and 64 rows (or
+// 256 and 128 keys), so groups cost 6-9 % (two) and 20-40 % (four) of the rate
+// and pay where they fill idle CUs or even out the causal ramp:
+//   8,192 queries x 8,192 earlier keys, 1 head: forward 183 / 105 / 76 us with
+//     1 / 2 / 4 groups, dQ 229 / 130 / 84, dK/dV 325 / 185;
+//   16,384 x 16,384 of the diagonal, 4 heads: 415 / 273 / 340, 560 / 361 / 404,
+//     770 / 490; the same not causal: 465 / 502 / 650, 643 / 680 / 770, 880 / 931;
+//   512 tokens x 8 heads of 64 (4-wave base): forward 12.1 / 10.6 / 8.2 us.
+double est_unsplit_us(Which k, const Job& j, const Shape& sh) {
+  static constexpr double kUnit[3][3] = {{3.4, 1.85, 1.2}, {4.6, 2.45, 1.45}, {3.2, 1.72, 0}};
+  constexpr double kWorkgroupUs = 5.0;  // a workgroup's start and end
+  const int tile = sh.tile();
+  const bool kv = k == DKDV;
+  const Sizes &mine = kv ? j.sk : j.sq, &other = kv ? j.sq : j.sk;
+  const int64_t heads = kv ? j.sk.hkv : j.sq.hq, g = kv ? j.sq.hq / j.sq.hkv : 1;
+  const int64_t step = kv ? 64 : 128, n = tiles_of(mine, tile);
+  int64_t total = 0, most = 0, least = INT64_MAX;
+  for (int64_t i = 0; i < n; ++i) {
+    int64_t seen = other.T;  // rows or keys that the tile visits
+    if (j.causal)
+      seen = kv ? other.T - std::min(other.T, std::max<int64_t>(0, i * tile - j.shift))
+                : std::max<int64_t>(0, std::min(other.T, (i + 1) * tile + j.shift));
+    const int64_t u = (seen + step - 1) / step * g;
+    total += u;
+    most = std::max(most, u);
+    least = std::min(least, u);
+  }
+  const double rounds = (double)(n * heads) / kCUs, whole = std::ceil(rounds);
+  // heaviest first over the CUs: the mean load, plus a light item in the last
+  // round where it is not full
+  const double units = std::max((double)most, (double)total * heads / kCUs + (whole - rounds) * least);
+  // (a 4-wave workgroup alone on its CU: half the rows of an 8-wave one)
+  const double unit = sh.nw == 4 ? 0.6 * kUnit[k][0] : kUnit[k][sh.groups / 2];
+  return whole * kWorkgroupUs + units * unit * (j.sq.d == 64 ? 0.7 : 1.0);
 }
 
-// the heaviest key tile visits every 64-row query step of every head of its group
-pdy::Split dkdv_split(const Sizes& sq, const Sizes& sk, int causal, bool chunk) {
-  const int rows = pdy::DkdvCfg<128>::BQ;
-  const int g = (int)(sq.hq / sq.hkv);
-  const double unit = tile_us((double)rows * kKvTile, sq, 8.0, 4.5);
-  const double slice = 2.0 * sk.T * sk.hkv * sk.d * 4;
-  const int p = split_parts(grid_items(sk, kKvTile) * sk.hkv, (int64_t)tiles_of(sq, rows) * g,
-                            unit, slice);
-  pdy::Split shape = uniform_split(1);
-  shape.kind = 1;
-  shape.nitems = tiles_of(sk, kKvTile);
-  shape.total = (int)sk.T;
-  shape.causal = causal;
-  shape.rows = rows;
-  shape.keys = kKvTile;
-  shape.group = g;
-  return choose_split(p, sk, causal, chunk || sk.T == 0, shape, sk.hkv, unit, slice);
+// launches of this many workgroups fill the chip in any shape
+constexpr int64_t kManyItems = 1024;
+
+Launch pick(Which k, const Job& j) {
+  const Launch base = base_launch(k, j);
+  const Work w = work_of(k, j, base.sh);
+  const int64_t n = w.items * w.heads;
+  auto shape = [&](int groups) { return Shape{8, groups}; };
+  if (j.sq.N > 1) {
+    // packed batches: dK/dV over 128-key tiles where 256-key ones leave CUs idle
+    // (4,096 tokens in 8 segments, 16/4 heads of 64: 47.6 -> 37.4 us)
+    if (k != DKDV || n >= kCUs) return base;
+    const Work w2 = work_of(k, j, shape(2));
+    return {shape(2), split_of(w2, j, std::max(1, base.split.parts / 2))};
+  }
+  if (base.split.parts > 1) {
+    // Two groups of half as many parts: as many workgroups and half the partial
+    // results, but products 5-7 % slower (d = 64, whose partial results are half
+    // as large: 10-12 %), so for launches that are not long.  Single sequences of
+    // d = 128, all combining included: 2,500 tokens x 6/2 heads backward 82 -> 73
+    // us, 6,144 x 1 forward 32.7 -> 28.7 and backward 77 -> 69, 8,192 x 4 92 -> 88
+    // and 281 -> 266; 16,384 x 4, no longer split, 288 -> 274 and 880 -> 856;
+    // 10,153 x 2 of d = 64 would lose (67 -> 71 and 156 -> 164).  (Not for the
+    // 4-wave query-tile kernels: no gain.)
+    if (base.sh.nw == 4) return base;
+    static constexpr double kSlower[2][3] = {{0.12, 0.10, 0.10}, {0.07, 0.05, 0.05}};
+    constexpr double kMovedBytesPerUs = 5.0e6;
+    const int p = split_parts(n, w.inner, w.unit_us, w.slice);
+    const double longest = base.split.cap ? base.split.cap : (double)((w.inner + p - 1) / p);
+    const double mean = (double)n / kCUs * w.inner * (j.causal ? 0.5 : 1.0);
+    const double us = std::max(longest, mean) * w.unit_us;
+    const double saved_us = p * w.slice / kMovedBytesPerUs + (p == 2 ? kLaunchUs : 0.0);
+    if (kSlower[j.sq.d == 128][k] * us > saved_us) return base;
+    const Work w2 = work_of(k, j, shape(2));
+    return {shape(2), split_of(w2, j, p / 2)};
+  }
+  // a 4-wave launch that has a workgroup for every CU is left alone
+  if (j.sk.T == 0 || n >= (base.sh.nw == 4 ? kCUs + 1 : kManyItems)) return base;
+  if (j.chunk) {
+    // A pair whose two-group launch leaves half the chip idle or more is split
+    // (by its sizes alone: its workspace query knows no offsets).  A
+    // device's pairs of a zig-zag ring of 8 over 32,768 tokens x 4 heads (2,048
+    // rows each): forward 0.78 -> 0.62 ms, backward 2.75 -> 1.52; over 131,072
+    // (8,192 rows, groups without a split) 2.45 -> 2.50 on two streams, which
+    // two launches without groups just fill, and 9.76 -> 7.81.
+    const Work w2 = work_of(k, j, shape(2));
+    int p = 1;
+    while (p < kMaxSplit && w2.items * w2.heads * p * 2 <= kCUs && w2.inner >= 8 * p) p *= 2;
+    if (p > 1) return {shape(2), split_of(w2, j, p)};
+  }
+  Launch best = base;
+  double t = 0.97 * est_unsplit_us(k, j, base.sh);
+  for (int groups = 2; groups <= (k == DKDV ? 2 : 4); groups *= 2) {
+    const double e = est_unsplit_us(k, j, shape(groups));
+    if (e < t) {
+      t = e;
+      best.sh = shape(groups);
+    }
+  }
+  return best;
 }
 
 size_t part_o_bytes(const Sizes& s, int p) { return align256((size_t)p * s.T * s.hq * s.d * 4); }
@@ -370,19 +503,53 @@ size_t bwd_split_bytes(const pdy::Split& kv, const pdy::Split& q, const Sizes& s
          (q.parts > 1 ? part_o_bytes(sq, q.parts) : 0);
 }
 
-// workspace of a (non-chunk) backward, causal or not: both tile schedules, D
-// and any split-K partials
-size_t bwd_workspace_bytes(const Sizes& s) {
-  size_t parts = 0;
-  for (int causal = 0; causal <= 1; ++causal)
-    parts = std::max(parts, bwd_split_bytes(dkdv_split(s, s, causal, false),
-                                            dq_split(s, s, causal, false), s, s));
-  return plan_bytes(s, kKvTile) + plan_bytes(s, 32 * fwd_waves(s)) + dd_bytes(s) + parts;
-}
-
 // A single segment (N = 1: by the contract cu = [0, T], and max_seqlen = T)
 // needs no schedule: item i is its level nt - 1 - i, so no plan is built.
 bool needs_plan(const Sizes& s) { return s.N > 1; }
+
+// Space of a launch's schedule; a single segment's is not used and has the size
+// of the base shape's, so that its callers' workspaces do not depend on the shape.
+size_t q_plan_bytes(const Sizes& s, const Shape& sh) {
+  return plan_bytes(s, (needs_plan(s) ? sh : base_shape(FWD, s)).tile());
+}
+size_t kv_plan_bytes(const Sizes& s, const Shape& sh) {
+  return plan_bytes(s, (needs_plan(s) ? sh : base_shape(DKDV, s)).tile());
+}
+
+// Workspace of a forward: schedule and any split-K partials.
+size_t fwd_need(const Launch& l, const Sizes& sq) {
+  return q_plan_bytes(sq, l.sh) + fwd_split_bytes(l.split, sq);
+}
+
+// Workspace of a backward without its split-K partials: both schedules and D
+// (sk: sizes of the key side, the query side for self-attention), and with them.
+size_t bwd_fixed(const Shape& kv, const Shape& q, const Sizes& sq, const Sizes& sk) {
+  return kv_plan_bytes(sk, kv) + q_plan_bytes(sq, q) + dd_bytes(sq);
+}
+size_t bwd_need(const Launch& kv, const Launch& q, const Sizes& sq, const Sizes& sk) {
+  return bwd_fixed(kv.sh, q.sh, sq, sk) + bwd_split_bytes(kv.split, q.split, sq, sk);
+}
+
+// What the workspace queries return: enough for the picked launches and for the
+// base ones, causal or not.  (A chunk pair's split does not depend on its
+// offsets.)
+size_t fwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
+  size_t n = 0;
+  for (int causal = 0; causal <= 1; ++causal) {
+    const Job j{sq, sk, causal, chunk, 0};
+    n = std::max({n, fwd_need(pick(FWD, j), sq), fwd_need(base_launch(FWD, j), sq)});
+  }
+  return n;
+}
+size_t bwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
+  size_t n = 0;
+  for (int causal = 0; causal <= 1; ++causal) {
+    const Job j{sq, sk, causal, chunk, 0};
+    n = std::max({n, bwd_need(pick(DKDV, j), pick(DQ, j), sq, sk),
+                  bwd_need(base_launch(DKDV, j), base_launch(DQ, j), sq, sk)});
+  }
+  return n;
+}
 
 // segment-major work order from this many tiles in the longest segment on
 constexpr int kSegMajorTiles = 8;
@@ -410,42 +577,68 @@ hipError_t set_lds(K kernel, int bytes) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
+template <int D, int NW, int KG>
+hipError_t launch_fwd(const pdy::FwdArgs* a, dim3 grid, hipStream_t st) {
+  using C = pdy::FwdCfg<D, NW, KG>;
+  if (a == nullptr) return set_lds(pdy::fwd_kernel<D, NW, KG>, C::LDS_BYTES);
+  hipLaunchKernelGGL((pdy::fwd_kernel<D, NW, KG>), grid, dim3(C::NT), C::LDS_BYTES, st, *a);
+  return hipSuccess;
+}
+
+template <int D, int NW, int KG>
+hipError_t launch_dq(const pdy::BwdArgs* a, dim3 grid, hipStream_t st) {
+  using C = pdy::DqCfg<D, NW, KG>;
+  if (a == nullptr) return set_lds(pdy::bwd_dq_kernel<D, NW, KG>, C::LDS_BYTES);
+  hipLaunchKernelGGL((pdy::bwd_dq_kernel<D, NW, KG>), grid, dim3(C::NT), C::LDS_BYTES, st, *a);
+  return hipSuccess;
+}
+
+template <int D, int QG>
+hipError_t launch_dkdv(const pdy::BwdArgs* a, dim3 grid, hipStream_t st) {
+  using C = pdy::DkdvCfg<D, QG>;
+  if (a == nullptr) return set_lds(pdy::bwd_dkdv_kernel<D, QG>, C::LDS_BYTES);
+  hipLaunchKernelGGL((pdy::bwd_dkdv_kernel<D, QG>), grid, dim3(C::NT), C::LDS_BYTES, st, *a);
+  return hipSuccess;
+}
+
+// The kernels by shape; called without arguments they set their attributes.
+struct Kernels {
+  int nw, groups;
+  hipError_t (*fwd[2])(const pdy::FwdArgs*, dim3, hipStream_t);  // d = 64, 128
+  hipError_t (*dq[2])(const pdy::BwdArgs*, dim3, hipStream_t);
+};
+constexpr Kernels kQKernels[] = {
+    {4, 1, {launch_fwd<64, 4, 1>, launch_fwd<128, 4, 1>}, {launch_dq<64, 4, 1>, launch_dq<128, 4, 1>}},
+    {8, 1, {launch_fwd<64, 8, 1>, launch_fwd<128, 8, 1>}, {launch_dq<64, 8, 1>, launch_dq<128, 8, 1>}},
+    {8, 2, {launch_fwd<64, 8, 2>, launch_fwd<128, 8, 2>}, {launch_dq<64, 8, 2>, launch_dq<128, 8, 2>}},
+    {8, 4, {launch_fwd<64, 8, 4>, launch_fwd<128, 8, 4>}, {launch_dq<64, 8, 4>, launch_dq<128, 8, 4>}},
+};
+hipError_t (*const kDkdvKernels[2][2])(const pdy::BwdArgs*, dim3, hipStream_t) = {
+    {launch_dkdv<64, 1>, launch_dkdv<128, 1>}, {launch_dkdv<64, 2>, launch_dkdv<128, 2>}};
+
+const Kernels& q_kernels(const Shape& sh) {
+  for (const Kernels& k : kQKernels)
+    if (k.nw == sh.nw && k.groups == sh.groups) return k;
+  return kQKernels[1];  // (not reached: every shape the launches use is listed)
+}
+
 // One-time per-process kernel attribute setup (LDS above the 64 KiB default).
 hipError_t init_kernels() {
   static hipError_t status = [] {
-    hipError_t e;
-    if ((e = set_lds(pdy::fwd_kernel<64, 4>, pdy::FwdCfg<64, 4>::LDS_BYTES)) != hipSuccess) return e;
-    if ((e = set_lds(pdy::fwd_kernel<64, 8>, pdy::FwdCfg<64, 8>::LDS_BYTES)) != hipSuccess) return e;
-    if ((e = set_lds(pdy::fwd_kernel<128, 4>, pdy::FwdCfg<128, 4>::LDS_BYTES)) != hipSuccess)
-      return e;
-    if ((e = set_lds(pdy::fwd_kernel<128, 8>, pdy::FwdCfg<128, 8>::LDS_BYTES)) != hipSuccess)
-      return e;
-    if ((e = set_lds(pdy::bwd_dkdv_kernel<64>, pdy::DkdvCfg<64>::LDS_BYTES)) != hipSuccess) return e;
-    if ((e = set_lds(pdy::bwd_dkdv_kernel<128>, pdy::DkdvCfg<128>::LDS_BYTES)) != hipSuccess)
-      return e;
-    if ((e = set_lds(pdy::bwd_dq_kernel<64, 4>, pdy::DqCfg<64, 4>::LDS_BYTES)) != hipSuccess)
-      return e;
-    if ((e = set_lds(pdy::bwd_dq_kernel<64, 8>, pdy::DqCfg<64, 8>::LDS_BYTES)) != hipSuccess)
-      return e;
-    if ((e = set_lds(pdy::bwd_dq_kernel<128, 4>, pdy::DqCfg<128, 4>::LDS_BYTES)) != hipSuccess)
-      return e;
-    if ((e = set_lds(pdy::bwd_dq_kernel<128, 8>, pdy::DqCfg<128, 8>::LDS_BYTES)) != hipSuccess)
-      return e;
+    for (int d = 0; d < 2; ++d) {
+      for (const Kernels& k : kQKernels) {
+        hipError_t e = k.fwd[d](nullptr, dim3(), nullptr);
+        if (e == hipSuccess) e = k.dq[d](nullptr, dim3(), nullptr);
+        if (e != hipSuccess) return e;
+      }
+      for (const auto& k : kDkdvKernels) {
+        const hipError_t e = k[d](nullptr, dim3(), nullptr);
+        if (e != hipSuccess) return e;
+      }
+    }
     return hipSuccess;
   }();
   return status;
-}
-
-template <int D, int NW>
-void launch_fwd(dim3 grid, hipStream_t st, const pdy::FwdArgs& a) {
-  using C = pdy::FwdCfg<D, NW>;
-  hipLaunchKernelGGL((pdy::fwd_kernel<D, NW>), grid, dim3(C::NT), C::LDS_BYTES, st, a);
-}
-
-template <int D, int NW>
-void launch_dq(dim3 grid, hipStream_t st, const pdy::BwdArgs& a) {
-  using C = pdy::DqCfg<D, NW>;
-  hipLaunchKernelGGL((pdy::bwd_dq_kernel<D, NW>), grid, dim3(C::NT), C::LDS_BYTES, st, a);
 }
 
 pdy_status check_scale(float scale, int32_t causal) {
@@ -501,16 +694,14 @@ size_t attn_fwd_workspace_size(int32_t T, int32_t N, int32_t maxlen, int32_t hq,
                                int32_t d) {
   Sizes s;
   if (check_sizes(T, N, maxlen, hq, hkv, d, &s) != PDY_OK) return 0;
-  return plan_bytes(s, 32 * fwd_waves(s)) +
-         std::max(fwd_split_bytes(fwd_split(s, s, 0, false), s),
-                  fwd_split_bytes(fwd_split(s, s, 1, false), s));
+  return fwd_workspace_bytes(s, s, false);
 }
 
 size_t attn_bwd_workspace_size(int32_t T, int32_t N, int32_t maxlen, int32_t hq, int32_t hkv,
                                int32_t d) {
   Sizes s;
   if (check_sizes(T, N, maxlen, hq, hkv, d, &s) != PDY_OK) return 0;
-  return bwd_workspace_bytes(s);
+  return bwd_workspace_bytes(s, s, false);
 }
 
 }  // extern "C"
@@ -532,17 +723,18 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
                     void* workspace, size_t workspace_bytes, void* stream, const Chunk& c,
                     const char* who) {
   pdy_status st;
-  const int nw = fwd_waves(s);
-  const int tile = 32 * nw;
-  // a context-parallel pair does not split: the ring already overlaps its
-  // forward calls on two streams, and the backward's partial traffic and
-  // extra launches cancel the gain (measured at 131,072 tokens over p = 8)
-  const pdy::Split split = fwd_split(s, sk, causal, c.on);
-  const int nsplit = split.parts;
-  const size_t need = plan_bytes(s, tile) + fwd_split_bytes(split, s);
+  const Job job{s, sk, causal, c.on != 0, c.shift};
+  Launch l = pick(FWD, job);
+  // (a pair whose workspace was sized for other chunks takes fewer parts)
+  while (c.on && workspace_bytes < fwd_need(l, s) && l.split.parts > 1)
+    l.split = halve_split(l.split);
+  if (workspace_bytes < fwd_need(l, s)) l = base_launch(FWD, job);
+  const size_t need = fwd_need(l, s);
   if (workspace_bytes < need)
     return fail(PDY_ERR_WORKSPACE, "workspace has %zu bytes, %s needs %zu", workspace_bytes, who,
                 need);
+  const pdy::Split& split = l.split;
+  const int nsplit = split.parts, tile = l.sh.tile();
   hipError_t e = init_kernels();
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
@@ -570,20 +762,12 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   a.part_o = nullptr;
   a.part_lse = nullptr;
   if (nsplit > 1) {
-    uint8_t* w = reinterpret_cast<uint8_t*>(workspace) + plan_bytes(s, tile);
+    uint8_t* w = reinterpret_cast<uint8_t*>(workspace) + q_plan_bytes(s, l.sh);
     a.part_o = reinterpret_cast<float*>(w);
     a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(s, nsplit));
   }
   const dim3 grid((unsigned)(split_entries(split, grid_items(s, tile)) * s.hq));
-  e = launch_timed(K_FWD, hs, [&] {
-    if (s.d == 64) {
-      if (nw == 8) launch_fwd<64, 8>(grid, hs, a);
-      else launch_fwd<64, 4>(grid, hs, a);
-    } else {
-      if (nw == 8) launch_fwd<128, 8>(grid, hs, a);
-      else launch_fwd<128, 4>(grid, hs, a);
-    }
-  });
+  e = launch_timed(K_FWD, hs, [&] { (void)q_kernels(l.sh).fwd[s.d == 128](&a, grid, hs); });
   if (e != hipSuccess) return hip_fail(e, "fwd_kernel launch");
   if (nsplit > 1) {
     const size_t threads = (size_t)s.T * s.hq * (s.d / 8);
@@ -602,51 +786,50 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   return PDY_OK;
 }
 
-// sk: sizes of the key side (the query side for self-attention)
-size_t bwd_need(const Sizes& s, const Sizes& sk) {
-  return plan_bytes(sk, kKvTile) + plan_bytes(s, 32 * fwd_waves(s)) + dd_bytes(s);
-}
-
 pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, const float* lse,
                     const void* dout, const int32_t* cu, const Sizes& s, const Sizes& sk,
                     int32_t causal, float scale, float* dq, float* dk, float* dv,
                     void* workspace, size_t workspace_bytes, void* stream, const Chunk& c,
-                    const char* who, bool fit_splits = false) {
+                    const char* who, bool fit_splits) {
   pdy_status st;
-  const int nwq = fwd_waves(s);
-  const int qtile = 32 * nwq;
-  // (no split-K for a context-parallel pair, as in the forward)
-  pdy::Split split_kv = dkdv_split(s, sk, causal, c.on);
-  pdy::Split split_q = dq_split(s, sk, causal, c.on);
-  // fit_splits: a fixed-size workspace takes fewer split-K parts (the larger
-  // partial buffer halved first) when the chosen ones do not fit
-  while (fit_splits && bwd_need(s, sk) + bwd_split_bytes(split_kv, split_q, s, sk) >
-                           workspace_bytes &&
-         (split_kv.parts > 1 || split_q.parts > 1)) {
-    const size_t bk = split_kv.parts > 1 ? 2 * part_kv_bytes(sk, split_kv.parts) : 0;
-    const size_t bq = split_q.parts > 1 ? part_o_bytes(s, split_q.parts) : 0;
-    if (bq >= bk) split_q = halve_split(split_q);
-    else split_kv = halve_split(split_kv);
+  const Job job{s, sk, causal, c.on != 0, c.shift};
+  Launch lk = pick(DKDV, job), lq = pick(DQ, job);
+  // fit_splits: a workspace of fixed size, or sized for other chunks, takes
+  // fewer split-K parts (the larger partial buffer halved first) when the chosen
+  // ones do not fit
+  auto fits = [&] {
+    while (fit_splits && bwd_need(lk, lq, s, sk) > workspace_bytes &&
+           (lk.split.parts > 1 || lq.split.parts > 1)) {
+      const size_t bk = lk.split.parts > 1 ? 2 * part_kv_bytes(sk, lk.split.parts) : 0;
+      const size_t bq = lq.split.parts > 1 ? part_o_bytes(s, lq.split.parts) : 0;
+      if (bq >= bk) lq.split = halve_split(lq.split);
+      else lk.split = halve_split(lk.split);
+    }
+    return bwd_need(lk, lq, s, sk) <= workspace_bytes;
+  };
+  if (!fits()) {
+    lk = base_launch(DKDV, job);
+    lq = base_launch(DQ, job);
+    if (!fits())
+      return fail(PDY_ERR_WORKSPACE, "workspace has %zu bytes, %s needs %zu", workspace_bytes, who,
+                  bwd_need(lk, lq, s, sk));
   }
+  const pdy::Split &split_kv = lk.split, &split_q = lq.split;
   const int nsplit_kv = split_kv.parts, nsplit_q = split_q.parts;
-  const size_t need = bwd_need(s, sk) + bwd_split_bytes(split_kv, split_q, s, sk);
-  if (workspace_bytes < need)
-    return fail(PDY_ERR_WORKSPACE, "workspace has %zu bytes, %s needs %zu", workspace_bytes, who,
-                need);
+  const int qtile = lq.sh.tile(), kvtile = lk.sh.tile();
   hipError_t e = init_kernels();
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
-  int32_t* ws = reinterpret_cast<int32_t*>(workspace);
-  int32_t* ws_q = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(workspace) +
-                                              plan_bytes(sk, kKvTile));
-  float* dd = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(workspace) +
-                                       plan_bytes(sk, kKvTile) + plan_bytes(s, qtile));
+  uint8_t* const wsb = reinterpret_cast<uint8_t*>(workspace);
+  int32_t* ws = reinterpret_cast<int32_t*>(wsb);
+  int32_t* ws_q = reinterpret_cast<int32_t*>(wsb + kv_plan_bytes(sk, lk.sh));
+  float* dd = reinterpret_cast<float*>(wsb + kv_plan_bytes(sk, lk.sh) + q_plan_bytes(s, lq.sh));
 
   {
     // the query-tile schedule, and the key-tile one unless there are no keys
     // (the key side has the same segments as the query side, or is a chunk)
     const pdy::PlanJob q_job = plan_job(cu, ws_q, s, qtile);
-    const pdy::PlanJob kv_job = plan_job(cu, ws, sk, kKvTile);
+    const pdy::PlanJob kv_job = plan_job(cu, ws, sk, kvtile);
     if (needs_plan(s) &&
         (st = launch_plans(q_job, sk.T > 0 ? &kv_job : nullptr, hs)) != PDY_OK)
       return st;
@@ -663,7 +846,7 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   a.dq = dq;
   a.dk = dk;
   a.dv = dv;
-  a.plan = make_plan(ws, sk, kKvTile);
+  a.plan = make_plan(ws, sk, kvtile);
   a.plan_q = make_plan(ws_q, s, qtile);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
@@ -679,7 +862,7 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   a.split_q = split_q;
   a.part_dk = a.part_dv = a.part_dq = nullptr;
   {
-    uint8_t* w = reinterpret_cast<uint8_t*>(workspace) + bwd_need(s, sk);
+    uint8_t* w = wsb + bwd_fixed(lk.sh, lq.sh, s, sk);
     if (nsplit_kv > 1) {
       a.part_dk = reinterpret_cast<float*>(w);
       a.part_dv = reinterpret_cast<float*>(w + part_kv_bytes(sk, nsplit_kv));
@@ -689,25 +872,12 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   }
   // dQ first: it also writes D = rowsum(dO * O), which dK/dV reads
   const dim3 gq((unsigned)(split_entries(split_q, grid_items(s, qtile)) * s.hq));
-  e = launch_timed(K_DQ, hs, [&] {
-    if (s.d == 64) {
-      if (nwq == 8) launch_dq<64, 8>(gq, hs, a);
-      else launch_dq<64, 4>(gq, hs, a);
-    } else {
-      if (nwq == 8) launch_dq<128, 8>(gq, hs, a);
-      else launch_dq<128, 4>(gq, hs, a);
-    }
-  });
+  e = launch_timed(K_DQ, hs, [&] { (void)q_kernels(lq.sh).dq[s.d == 128](&a, gq, hs); });
   if (e != hipSuccess) return hip_fail(e, "bwd_dq_kernel launch");
   if (sk.T > 0) {
-    const dim3 gkv((unsigned)(split_entries(split_kv, grid_items(sk, kKvTile)) * s.hkv));
+    const dim3 gkv((unsigned)(split_entries(split_kv, grid_items(sk, kvtile)) * s.hkv));
     e = launch_timed(K_DKDV, hs, [&] {
-      if (s.d == 64)
-        hipLaunchKernelGGL(pdy::bwd_dkdv_kernel<64>, gkv, dim3(pdy::DkdvCfg<64>::NT),
-                           pdy::DkdvCfg<64>::LDS_BYTES, hs, a);
-      else
-        hipLaunchKernelGGL(pdy::bwd_dkdv_kernel<128>, gkv, dim3(pdy::DkdvCfg<128>::NT),
-                           pdy::DkdvCfg<128>::LDS_BYTES, hs, a);
+      (void)kDkdvKernels[lk.sh.groups - 1][s.d == 128](&a, gkv, hs);
     });
     if (e != hipSuccess) return hip_fail(e, "bwd_dkdv_kernel launch");
   }
@@ -841,13 +1011,13 @@ pdy_status attn_fwd(const void* q, const void* k, const void* v, const int32_t* 
 size_t attn_fwd_chunk_workspace_size(int32_t tq, int32_t tk, int32_t hq, int32_t hkv, int32_t d) {
   Sizes sq, sk;
   if (chunk_sizes(tq, tk, hq, hkv, d, &sq, &sk) != PDY_OK) return 0;
-  return plan_bytes(sq, 32 * fwd_waves(sq));
+  return fwd_workspace_bytes(sq, sk, true);
 }
 
 size_t attn_bwd_chunk_workspace_size(int32_t tq, int32_t tk, int32_t hq, int32_t hkv, int32_t d) {
   Sizes sq, sk;
   if (chunk_sizes(tq, tk, hq, hkv, d, &sq, &sk) != PDY_OK) return 0;
-  return bwd_need(sq, sk);
+  return bwd_workspace_bytes(sq, sk, true);
 }
 
 pdy_status attn_fwd_chunk(const void* q, const void* k, const void* v, int32_t tq, int32_t tk,
@@ -890,7 +1060,7 @@ pdy_status attn_bwd(const void* q, const void* k, const void* v, const void* o, 
     return st;
   if ((st = check_ptr(workspace, "workspace")) != PDY_OK) return st;
   return bwd_impl(q, k, v, o, lse, dout, cu_seqlens, s, s, causal, scale, dq, dk, dv, workspace,
-                  workspace_bytes, stream, Chunk{}, "attn_bwd");
+                  workspace_bytes, stream, Chunk{}, "attn_bwd", false);
 }
 
 pdy_status attn_bwd_noalloc(const void* q, const void* k, const void* v, const void* o,
@@ -909,7 +1079,7 @@ pdy_status attn_bwd_noalloc(const void* q, const void* k, const void* v, const v
     return st;
   // the scratch attn_bwd takes from its workspace: the tile schedules and D,
   // plus split-K partial gradients where those fit (else fewer parts)
-  const size_t need = bwd_need(s, s);
+  const size_t need = bwd_fixed(base_shape(DKDV, s), base_shape(FWD, s), s, s);
   if (need > kScratchBytes)
     return fail(PDY_ERR_WORKSPACE,
                 "attn_bwd_noalloc needs %zu bytes of scratch for these sizes, more than its "
@@ -964,7 +1134,7 @@ pdy_status attn_bwd_chunk(const void* q, const void* k, const void* v, const voi
   c.shift = q_offset - k_offset;
   c.accumulate = accumulate;
   return bwd_impl(q, k, v, o, lse, dout, nullptr, sq, sk, causal, scale, dq, dk, dv, workspace,
-                  workspace_bytes, stream, c, "attn_bwd_chunk");
+                  workspace_bytes, stream, c, "attn_bwd_chunk", /*fit_splits=*/true);
 }
 
 pdy_status attn_merge(const void* o_a, const float* lse_a, const void* o_b, const float* lse_b,

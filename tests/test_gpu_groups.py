@@ -1,0 +1,106 @@
+"""Key groups (forward, dQ) and query groups (dK/dV): workgroups of small
+launches whose waves share the rows (keys) and split the inner loop, combined in
+LDS.  Every element against the fp64 oracle at the sizes where the groups begin,
+end or leave waves without work; the same results from a workspace that only
+holds the launch without groups and parts."""
+import numpy as np
+import pytest
+
+from oracle import attention as ora
+from paper_2511_13198_amd import workloads as wl
+from tests.parity_util import check_close, log, to_device_bf16
+from tests.test_gpu_chunks import _check_partial, _dev, _host
+from tests.test_gpu_parity import _full_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,causal", [
+    ([1], 1, 1, 64, True),            # one row, one key: 3 of 4 groups see nothing
+    ([65], 3, 1, 128, True),          # a 64-row tile and one row
+    ([512], 8, 8, 64, True),          # four groups, unsplit
+    ([511], 2, 2, 128, False),
+    ([2049], 1, 1, 128, True),        # two groups, balanced parts, one row in the last tile
+    ([2500], 6, 2, 64, True),         # three query heads per key head
+    ([2304], 2, 1, 128, False),       # two groups, uniform parts
+    ([300, 1, 129, 512], 2, 1, 64, True),   # packed: dK/dV over 128-key tiles
+    ([300, 0, 127], 4, 4, 128, False),
+])
+def test_groups_full_parity(lengths, hq, hkv, d, causal):
+    _full_parity(lengths, hq, hkv, d, causal)
+
+
+PAIRS = [
+    # (T, hq, hkv, d, causal, (qa, qb), (ka, kb)); the diagonal, an earlier, a
+    # later and an overlapping key chunk, ragged ends, over and under 2,048 rows
+    (4700, 1, 1, 128, True, (2400, 4700), (0, 2399)),
+    (2305, 1, 1, 128, True, (0, 2305), (0, 2305)),
+    (4600, 2, 1, 64, True, (2300, 4600), (2300, 4600)),
+    (3000, 1, 1, 128, True, (100, 2500), (1700, 3000)),
+    (900, 3, 1, 128, True, (200, 765), (0, 566)),
+    (1300, 2, 2, 64, False, (0, 1), (1, 1300)),
+    (2700, 1, 1, 64, True, (0, 300), (300, 2700)),   # nothing visible
+    (10000, 4, 4, 128, True, (8192, 8256), (0, 8192)),
+]
+
+
+@pytest.mark.parametrize("T,hq,hkv,d,causal,qs,ks", PAIRS)
+def test_group_pairs(T, hq, hkv, d, causal, qs, ks):
+    """Partial forward, the pair's gradients, and both again from the smallest
+    accepted workspace and added to what the gradients hold."""
+    import torch
+    from paper_2511_13198_amd import pdyattn
+    bits, f = _host(T, hq, hkv, d, 23)
+    scale = 1.0 / np.sqrt(d)
+    (qa, qb), (ka, kb) = qs, ks
+    tq, tk = qb - qa, kb - ka
+    log(f"  T={T} chunk q[{qa},{qb}) k[{ka},{kb}) Hq={hq} Hkv={hkv} d={d} causal={causal}")
+    o_ref, l_ref = ora.partial_forward(f["q"][qa:qb], f["k"][ka:kb], f["v"][ka:kb], qa, ka,
+                                       causal, scale)
+    q, do = _dev(bits, "q", qa, qb), _dev(bits, "do", qa, qb)
+    k, v = _dev(bits, "k", ka, kb), _dev(bits, "v", ka, kb)
+    # schedule space (unused) and D, no partial results
+    small = 4096 + 4 * hq * tq + 64 * (tq + tk)
+    ws = [None, torch.empty(small, dtype=torch.uint8, device="cuda")]
+    for w in ws:
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((hq, tq), float("nan"), dtype=torch.float32, device=q.device)
+        pdyattn.attn_fwd_chunk(q, k, v, qa, ka, causal, scale, out=o, lse=lse, workspace=w)
+        torch.cuda.synchronize()
+        _check_partial("O", "LSE", o.double().cpu().numpy(), lse.cpu().numpy(), o_ref, l_ref)
+    O, L = ora.forward(f["q"], f["k"], f["v"], np.array([0, T]), causal, scale)
+    o_bits = wl.f32_to_bf16_bits(O[qa:qb].astype(np.float32))
+    l32 = np.ascontiguousarray(L[:, qa:qb].astype(np.float32))
+    ref = ora.partial_backward(f["q"][qa:qb], f["k"][ka:kb], f["v"][ka:kb],
+                               wl.bf16_bits_to_f64(o_bits), l32.astype(np.float64), f["do"][qa:qb],
+                               qa, ka, causal, scale)
+    o_d, l_d = to_device_bf16(o_bits), torch.from_numpy(l32).cuda()
+    for w, add in ((None, False), (ws[1], False), (None, True)):
+        g = [torch.full(s, 0.5 if add else float("nan"), dtype=torch.float32, device="cuda")
+             for s in ((tq, hq, d), (tk, hkv, d), (tk, hkv, d))]
+        pdyattn.attn_bwd_chunk(q, k, v, o_d, l_d, do, qa, ka, causal, scale, dq=g[0], dk=g[1],
+                               dv=g[2], workspace=w, accumulate=add)
+        torch.cuda.synchronize()
+        for nm, got, r in zip(("dQc", "dKc", "dVc"), g, ref):
+            got = got.double().cpu().numpy() - (0.5 if add else 0.0)
+            if not np.any(r):
+                assert not np.any(got), f"{nm}: nonzero gradient for an invisible pair"
+            else:
+                check_close(nm, got, r)
+
+
+def test_underfilled_pairs_split():
+    """A pair whose workgroups fill less than half the chip takes partial
+    results; one that fills it, and any pair in a small workspace, does not."""
+    import torch
+    from paper_2511_13198_amd import pdyattn
+    for t, h, expect in ((4096, 1, True), (8192, 4, False)):
+        x = wl.device_inputs(t, h, h, 128, seed=3)
+        pdyattn.profile_start()
+        pdyattn.attn_fwd_chunk(x["q"], x["k"], x["v"], t, 0)
+        got = "split_merge_kernel" in pdyattn.profile_stop()
+        assert got == expect
+        ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+        pdyattn.profile_start()
+        pdyattn.attn_fwd_chunk(x["q"], x["k"], x["v"], t, 0, workspace=ws)
+        assert "split_merge_kernel" not in pdyattn.profile_stop()
