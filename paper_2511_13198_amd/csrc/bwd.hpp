@@ -79,7 +79,6 @@ struct BwdArgs {
   const uint16_t* dout;
   const float* lse;  // natural log, [Hq, T]
   float* dd;         // D = rowsum(dO * O), [Hq, T]: written by the dQ kernel, read by dK/dV
-  const int32_t* cu;
   float* dq;
   float* dk;
   float* dv;
@@ -94,7 +93,7 @@ struct BwdArgs {
   // chunk mode (chunked != 0): one query chunk of total_tokens rows against
   // one key/value chunk of tk rows of the same sequence; key j is visible to
   // row i (causal) iff j <= i + shift.  Otherwise rows and keys share the
-  // packed segments of cu.
+  // packed segments of plan.cu.
   int chunked;
   int tk;
   int shift;
@@ -170,12 +169,10 @@ __global__ void __launch_bounds__(512, D == 64 ? 3 : 1) bwd_dkdv_kernel(BwdArgs 
   int hk, entry, item, part, nparts;
   xcd_order(blockIdx.x, gridDim.x, a.hkv, hk, entry);
   if (!split_entry(a.split_kv, entry, item, part, nparts)) return;
-  int seg, level;
-  if (!plan_lookup(a.plan, item, seg, level)) return;
   // keys [k_lo, k_hi) (this workgroup: a tile of them), query rows
   // [q_lo, q_hi); causal: key j visible to row i iff j <= i + shift
-  const int k_lo = a.chunked ? 0 : a.cu[seg];
-  const int k_hi = a.chunked ? a.tk : a.cu[seg + 1];
+  int k_lo, k_hi = a.chunked ? a.tk : a.total_tokens, level;
+  if (!plan_lookup(a.plan, item, k_lo, k_hi, level)) return;
   const int q_lo = a.chunked ? 0 : k_lo;
   const int q_hi = a.chunked ? a.total_tokens : k_hi;
   const int shift = a.chunked ? a.shift : 0;
@@ -510,12 +507,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) bwd_dq_kernel(BwdArg
   int h, entry, item, part, nparts;
   xcd_order(blockIdx.x, gridDim.x, a.hq, h, entry);
   if (!split_entry(a.split_q, entry, item, part, nparts)) return;
-  int seg, level;
-  if (!plan_lookup(a.plan_q, item, seg, level)) return;
   // query rows [seg_lo, seg_hi), keys [k_lo, k_hi); causal: key j visible to
   // row i iff j <= i + shift
-  const int seg_lo = a.chunked ? 0 : a.cu[seg];
-  const int seg_hi = a.chunked ? a.total_tokens : a.cu[seg + 1];
+  int seg_lo, seg_hi = a.total_tokens, level;
+  if (!plan_lookup(a.plan_q, item, seg_lo, seg_hi, level)) return;
   const int k_lo = a.chunked ? 0 : seg_lo;
   const int k_hi = a.chunked ? a.tk : seg_hi;
   const int shift = a.chunked ? a.shift : 0;

@@ -75,7 +75,6 @@ struct FwdArgs {
   const uint16_t* q;
   const uint16_t* k;
   const uint16_t* v;
-  const int32_t* cu;
   uint16_t* o;
   float* lse;
   Plan plan;
@@ -87,7 +86,7 @@ struct FwdArgs {
   // chunk mode (chunked != 0): one query chunk of total_tokens rows over one
   // key/value chunk of tk rows of the same sequence; key j is visible to
   // row i (causal) iff j <= i + shift (shift = query offset - key offset).
-  // Otherwise rows and keys share the packed segments of cu.
+  // Otherwise rows and keys share the packed segments of plan.cu.
   int chunked;
   int tk;
   int shift;
@@ -212,12 +211,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
   int h, entry, item, part, nparts;
   xcd_order(blockIdx.x, gridDim.x, a.hq, h, entry);
   if (!split_entry(a.split, entry, item, part, nparts)) return;
-  int seg, level;
-  if (!plan_lookup(a.plan, item, seg, level)) return;
   // query rows [seg_lo, seg_hi), keys [k_lo, k_hi); causal: key j visible to
   // row i iff j <= i + shift
-  const int seg_lo = a.chunked ? 0 : a.cu[seg];
-  const int seg_hi = a.chunked ? a.total_tokens : a.cu[seg + 1];
+  int seg_lo, seg_hi = a.total_tokens, level;
+  if (!plan_lookup(a.plan, item, seg_lo, seg_hi, level)) return;
   const int k_lo = a.chunked ? 0 : seg_lo;
   const int k_hi = a.chunked ? a.tk : seg_hi;
   const int shift = a.chunked ? a.shift : 0;

@@ -504,16 +504,16 @@ size_t bwd_split_bytes(const pdy::Split& kv, const pdy::Split& q, const Sizes& s
 }
 
 // A single segment (N = 1: by the contract cu = [0, T], and max_seqlen = T)
-// needs no schedule: item i is its level nt - 1 - i, so no plan is built.
-bool needs_plan(const Sizes& s) { return s.N > 1; }
+// needs no schedule: item i is its level nt - 1 - i.
+bool packed(const Sizes& s) { return s.N > 1; }
 
 // Space of a launch's schedule; a single segment's is not used and has the size
 // of the base shape's, so that its callers' workspaces do not depend on the shape.
 size_t q_plan_bytes(const Sizes& s, const Shape& sh) {
-  return plan_bytes(s, (needs_plan(s) ? sh : base_shape(FWD, s)).tile());
+  return plan_bytes(s, (packed(s) ? sh : base_shape(FWD, s)).tile());
 }
 size_t kv_plan_bytes(const Sizes& s, const Shape& sh) {
-  return plan_bytes(s, (needs_plan(s) ? sh : base_shape(DKDV, s)).tile());
+  return plan_bytes(s, (packed(s) ? sh : base_shape(DKDV, s)).tile());
 }
 
 // Workspace of a forward: schedule and any split-K partials.
@@ -553,13 +553,24 @@ size_t bwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
 
 // segment-major work order from this many tiles in the longest segment on
 constexpr int kSegMajorTiles = 8;
+bool seg_major(const Sizes& s, int tile) { return tiles_of(s, tile) >= kSegMajorTiles; }
 
-pdy::Plan make_plan(int32_t* ws, const Sizes& s, int tile) {
+// Whether plan_kernel builds a schedule (few segments: the workgroups place
+// their items themselves).
+bool needs_plan(const Sizes& s, int tile) {
+  return s.N > (seg_major(s, tile) ? pdy::kDirectSegMajor : 64 * pdy::kDirectChunks);
+}
+
+pdy::Plan make_plan(const int32_t* cu, int32_t* ws, const Sizes& s, int tile) {
   const int nt = tiles_of(s, tile);
   pdy::Plan p;
+  p.cu = cu;
+  p.n = (int32_t)s.N;
+  p.direct = !needs_plan(s, tile);
+  p.tile_log2 = __builtin_ctz((unsigned)tile);  // every shape's tile is a power of two
   p.max_nt = nt;
-  p.seg_major = nt >= kSegMajorTiles;
-  if (!needs_plan(s)) {
+  p.seg_major = seg_major(s, tile);
+  if (p.direct) {
     p.order = p.start = p.total = p.cnt = p.before = nullptr;
     return p;
   }
@@ -739,17 +750,17 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   int32_t* ws = reinterpret_cast<int32_t*>(workspace);
-  if (needs_plan(s) && (st = launch_plans(plan_job(cu, ws, s, tile), nullptr, hs)) != PDY_OK)
+  if (needs_plan(s, tile) &&
+      (st = launch_plans(plan_job(cu, ws, s, tile), nullptr, hs)) != PDY_OK)
     return st;
 
   pdy::FwdArgs a;
   a.q = static_cast<const uint16_t*>(q);
   a.k = static_cast<const uint16_t*>(k);
   a.v = static_cast<const uint16_t*>(v);
-  a.cu = cu;
   a.o = static_cast<uint16_t*>(o);
   a.lse = lse;
-  a.plan = make_plan(ws, s, tile);
+  a.plan = make_plan(cu, ws, s, tile);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
   a.hkv = (int)s.hkv;
@@ -826,13 +837,15 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   float* dd = reinterpret_cast<float*>(wsb + kv_plan_bytes(sk, lk.sh) + q_plan_bytes(s, lq.sh));
 
   {
-    // the query-tile schedule, and the key-tile one unless there are no keys
-    // (the key side has the same segments as the query side, or is a chunk)
+    // the query-tile schedule and the key-tile one, where they are needed
+    // (packed batches: both sides have the same segments)
     const pdy::PlanJob q_job = plan_job(cu, ws_q, s, qtile);
     const pdy::PlanJob kv_job = plan_job(cu, ws, sk, kvtile);
-    if (needs_plan(s) &&
-        (st = launch_plans(q_job, sk.T > 0 ? &kv_job : nullptr, hs)) != PDY_OK)
-      return st;
+    const bool need_q = needs_plan(s, qtile), need_kv = needs_plan(sk, kvtile);
+    if (need_q || need_kv) {
+      st = launch_plans(need_q ? q_job : kv_job, need_q && need_kv ? &kv_job : nullptr, hs);
+      if (st != PDY_OK) return st;
+    }
   }
   pdy::BwdArgs a;
   a.q = static_cast<const uint16_t*>(q);
@@ -842,12 +855,11 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   a.dout = static_cast<const uint16_t*>(dout);
   a.lse = lse;
   a.dd = dd;
-  a.cu = cu;
   a.dq = dq;
   a.dk = dk;
   a.dv = dv;
-  a.plan = make_plan(ws, sk, kvtile);
-  a.plan_q = make_plan(ws_q, s, qtile);
+  a.plan = make_plan(cu, ws, sk, kvtile);
+  a.plan_q = make_plan(cu, ws_q, s, qtile);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
   a.hkv = (int)s.hkv;

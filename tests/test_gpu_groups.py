@@ -30,6 +30,28 @@ def test_groups_full_parity(lengths, hq, hkv, d, causal):
     _full_parity(lengths, hq, hkv, d, causal)
 
 
+@pytest.mark.parametrize("nseg,hi,hq,d", [
+    (2, 4000, 1, 128), (64, 1100, 2, 64), (65, 1100, 2, 64),   # segment-major, to 64 segments
+    (63, 500, 2, 128), (128, 500, 1, 64), (129, 500, 1, 64),   # level-major, to 128
+])
+def test_packed_placement(nseg, hi, hq, d):
+    """Packed batches on both sides of the segment counts up to which the
+    workgroups place their items themselves: every element (an item placed
+    twice, wrongly or not at all shows), equal counts and empty segments among
+    them, and the schedule kernel runs only beyond."""
+    from paper_2511_13198_amd import pdyattn
+    rng = np.random.default_rng(nseg)
+    lengths = [int(x) for x in rng.integers(1, hi + 1, size=nseg)]
+    lengths[0] = hi                    # the longest, so that the order is known
+    lengths[-1] = 0
+    if nseg > 2:
+        lengths[1] = lengths[2]
+    pdyattn.profile_start()
+    _full_parity(lengths, hq, hq, d, True)
+    ran = "plan_kernel" in pdyattn.profile_stop()
+    assert ran == (nseg in (65, 129))
+
+
 PAIRS = [
     # (T, hq, hkv, d, causal, (qa, qb), (ka, kb)); the diagonal, an earlier, a
     # later and an overlapping key chunk, ragged ends, over and under 2,048 rows
