@@ -125,12 +125,17 @@ struct BwdArgs {
 // and a wave takes one 32-row half of every step.  The groups' partial dK and dV
 // meet in LDS at the end.  For launches whose 256-key tiles are too few to fill
 // the chip (half as many keys per workgroup, no partial results in memory).
-template <int D, int QG = 1>
+// NW = 4: 128 keys and, at d = 128, 32-row steps, so that two workgroups share a
+// CU and one's start and end overlap the other's steps: for packed batches of
+// short segments, whose 256-key tiles are mostly padding and have few steps
+// (122 segments of 16-512 tokens x 32/8 heads: 190 -> 146 us).
+template <int D, int QG = 1, int NW_ = 8>
 struct DkdvCfg {
-  static constexpr int NW = 8;
+  static constexpr int NW = NW_;
   static constexpr int KW = NW / QG;    // waves along the keys
   static constexpr int BK = 32 * KW;    // keys per workgroup (32 per wave)
-  static constexpr int BQ = 64;         // query rows per step (two halves of 32)
+  // query rows per step (halves of 32; 32 rows of d = 64 are no whole copies)
+  static constexpr int BQ = NW == 4 && D == 128 ? 32 : 64;
   static constexpr int NT = NW * 64;
   using QL = DualLayout<D>;  // Q and dO: read as rows (S, dP) and transposed (dK, dV)
   using KL = RowsLayout<D>;  // K: read as rows only
@@ -152,9 +157,10 @@ struct DkdvCfg {
 // workgroup starts while half of the waves of one over a short segment still
 // store: 70 segments of 16-107 tokens x 16 heads 29 -> 25 us, and 21.5 with the
 // waves without keys ending before the stores)
-template <int D, int QG>
-__global__ void __launch_bounds__(512, D == 64 ? 3 : 1) bwd_dkdv_kernel(BwdArgs a) {
-  using C = DkdvCfg<D, QG>;
+template <int D, int QG, int NWAVES>
+__global__ void __launch_bounds__(NWAVES * 64, NWAVES == 4 ? 2 : D == 64 ? 3 : 1)
+    bwd_dkdv_kernel(BwdArgs a) {
+  using C = DkdvCfg<D, QG, NWAVES>;
   using QL = typename C::QL;
   using KL = typename C::KL;
   constexpr int BK = C::BK, BQ = C::BQ, NW = C::NW;
@@ -380,7 +386,8 @@ __global__ void __launch_bounds__(512, D == 64 ? 3 : 1) bwd_dkdv_kernel(BwdArgs 
     }
     using QD = TileDma<QL, BQ, NW>;
     constexpr int PQ = QD::PER_WAVE;  // copies of one tile per wave (at most)
-    static_assert(2 * PQ <= D / 16, "one copy per K-step of S/dP");
+    constexpr int NKS = D / 16;
+    static_assert(2 * (PQ - 1) <= NKS, "one copy per K-step of S/dP, and the last ones");
     QD qd;
     qd.init(qstride);
     auto issue = [&](int step, const StepPos& p) __attribute__((always_inline)) {
@@ -419,13 +426,14 @@ __global__ void __launch_bounds__(512, D == 64 ? 3 : 1) bwd_dkdv_kernel(BwdArgs 
           qd.issue_one(c, rsq, qbuf(bn));
         } else if constexpr (c < 2 * (PQ - 1)) {
           qd.issue_one(c - (PQ - 1), rsg, gbuf(bn));
-        } else if constexpr (c == D / 16 - 1) {
+        }
+        if constexpr (c == NKS - 1) {
           qd.issue_one(PQ - 1, rsq, qbuf(bn));
           qd.issue_one(PQ - 1, rsg, gbuf(bn));
         }
       });
       if (!ran && more) issue(step + 1, nxt);
-      if constexpr (QG == 1) compute(step, cur, 1, [](auto) {});
+      if constexpr (QG == 1 && BQ == 64) compute(step, cur, 1, [](auto) {});
       cur = nxt;
     }
   }

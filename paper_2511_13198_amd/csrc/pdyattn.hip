@@ -57,9 +57,8 @@ int tiles_of(const Sizes& s, int tile) {
 constexpr int64_t kShortSeg = 2048;
 int fwd_waves(const Sizes& s) { return s.maxlen > kShortSeg ? PDY_WAVES_LONG : 4; }
 
-// How a launch's workgroups are made up: forward and dQ by nw waves in `groups`
-// key groups (32 * nw / groups query rows each), dK/dV by 8 waves in `groups`
-// query groups (256 / groups keys each).
+// How a launch's workgroups are made up: nw waves in `groups` key groups (forward
+// and dQ, 32 * nw / groups query rows each) or query groups (dK/dV, as many keys).
 struct Shape {
   int nw;
   int groups;
@@ -425,6 +424,8 @@ double est_unsplit_us(Which k, const Job& j, const Shape& sh) {
   return whole * kWorkgroupUs + units * unit * (j.sq.d == 64 ? 0.7 : 1.0);
 }
 
+constexpr int64_t kAverageShort = 512;
+
 // launches of this many workgroups fill the chip in any shape
 constexpr int64_t kManyItems = 1024;
 
@@ -434,9 +435,20 @@ Launch pick(Which k, const Job& j) {
   const int64_t n = w.items * w.heads;
   auto shape = [&](int groups) { return Shape{8, groups}; };
   if (j.sq.N > 1) {
-    // packed batches: dK/dV over 128-key tiles where 256-key ones leave CUs idle
-    // (4,096 tokens in 8 segments, 16/4 heads of 64: 47.6 -> 37.4 us)
-    if (k != DKDV || n >= kCUs) return base;
+    // Packed batches, dK/dV over 128-key tiles:
+    //   * two 4-wave workgroups per CU where segments are short (on average, of
+    //     at most 512 tokens) and fill the chip: 122 of 16-512 tokens, 32/8 heads
+    //     190 -> 146 us, 420 of 16-119, 24/8 heads 192 -> 121, 70 of 16-107, 16
+    //     heads of 64 21.8 -> 18.7; 32 or 64 equal ones of 512 unchanged, of 1,024
+    //     0-15 % slower;
+    //   * two query groups where 256-key tiles leave CUs idle (4,096 tokens in 8
+    //     segments, 16/4 heads of 64: 47.6 -> 37.4 us).
+    if (k != DKDV) return base;
+    const Shape four{4, 1};
+    if (j.sk.maxlen <= kShortSeg && j.sk.T <= kAverageShort * j.sk.N &&
+        grid_items(j.sk, four.tile()) * w.heads >= 2 * kCUs)
+      return {four, uniform_split(1)};
+    if (n >= kCUs) return base;
     const Work w2 = work_of(k, j, shape(2));
     return {shape(2), split_of(w2, j, std::max(1, base.split.parts / 2))};
   }
@@ -604,46 +616,49 @@ hipError_t launch_dq(const pdy::BwdArgs* a, dim3 grid, hipStream_t st) {
   return hipSuccess;
 }
 
-template <int D, int QG>
+template <int D, int NW, int QG>
 hipError_t launch_dkdv(const pdy::BwdArgs* a, dim3 grid, hipStream_t st) {
-  using C = pdy::DkdvCfg<D, QG>;
-  if (a == nullptr) return set_lds(pdy::bwd_dkdv_kernel<D, QG>, C::LDS_BYTES);
-  hipLaunchKernelGGL((pdy::bwd_dkdv_kernel<D, QG>), grid, dim3(C::NT), C::LDS_BYTES, st, *a);
+  using C = pdy::DkdvCfg<D, QG, NW>;
+  if (a == nullptr) return set_lds(pdy::bwd_dkdv_kernel<D, QG, NW>, C::LDS_BYTES);
+  hipLaunchKernelGGL((pdy::bwd_dkdv_kernel<D, QG, NW>), grid, dim3(C::NT), C::LDS_BYTES, st, *a);
   return hipSuccess;
 }
 
-// The kernels by shape; called without arguments they set their attributes.
+// The kernels by shape (dK/dV has none of four groups); called without arguments
+// they set their attributes.
 struct Kernels {
   int nw, groups;
   hipError_t (*fwd[2])(const pdy::FwdArgs*, dim3, hipStream_t);  // d = 64, 128
   hipError_t (*dq[2])(const pdy::BwdArgs*, dim3, hipStream_t);
+  hipError_t (*dkdv[2])(const pdy::BwdArgs*, dim3, hipStream_t);
 };
-constexpr Kernels kQKernels[] = {
-    {4, 1, {launch_fwd<64, 4, 1>, launch_fwd<128, 4, 1>}, {launch_dq<64, 4, 1>, launch_dq<128, 4, 1>}},
-    {8, 1, {launch_fwd<64, 8, 1>, launch_fwd<128, 8, 1>}, {launch_dq<64, 8, 1>, launch_dq<128, 8, 1>}},
-    {8, 2, {launch_fwd<64, 8, 2>, launch_fwd<128, 8, 2>}, {launch_dq<64, 8, 2>, launch_dq<128, 8, 2>}},
-    {8, 4, {launch_fwd<64, 8, 4>, launch_fwd<128, 8, 4>}, {launch_dq<64, 8, 4>, launch_dq<128, 8, 4>}},
-};
-hipError_t (*const kDkdvKernels[2][2])(const pdy::BwdArgs*, dim3, hipStream_t) = {
-    {launch_dkdv<64, 1>, launch_dkdv<128, 1>}, {launch_dkdv<64, 2>, launch_dkdv<128, 2>}};
+template <int NW, int G>
+constexpr Kernels kernels_of() {
+  Kernels k{NW, G, {launch_fwd<64, NW, G>, launch_fwd<128, NW, G>},
+            {launch_dq<64, NW, G>, launch_dq<128, NW, G>}, {nullptr, nullptr}};
+  if constexpr (G <= 2) {
+    k.dkdv[0] = launch_dkdv<64, NW, G>;
+    k.dkdv[1] = launch_dkdv<128, NW, G>;
+  }
+  return k;
+}
+constexpr Kernels kKernels[] = {kernels_of<4, 1>(), kernels_of<8, 1>(), kernels_of<8, 2>(),
+                                kernels_of<8, 4>()};
 
-const Kernels& q_kernels(const Shape& sh) {
-  for (const Kernels& k : kQKernels)
+const Kernels& kernels(const Shape& sh) {
+  for (const Kernels& k : kKernels)
     if (k.nw == sh.nw && k.groups == sh.groups) return k;
-  return kQKernels[1];  // (not reached: every shape the launches use is listed)
+  return kKernels[1];  // (not reached: every shape the launches use is listed)
 }
 
 // One-time per-process kernel attribute setup (LDS above the 64 KiB default).
 hipError_t init_kernels() {
   static hipError_t status = [] {
     for (int d = 0; d < 2; ++d) {
-      for (const Kernels& k : kQKernels) {
+      for (const Kernels& k : kKernels) {
         hipError_t e = k.fwd[d](nullptr, dim3(), nullptr);
         if (e == hipSuccess) e = k.dq[d](nullptr, dim3(), nullptr);
-        if (e != hipSuccess) return e;
-      }
-      for (const auto& k : kDkdvKernels) {
-        const hipError_t e = k[d](nullptr, dim3(), nullptr);
+        if (e == hipSuccess && k.dkdv[d]) e = k.dkdv[d](nullptr, dim3(), nullptr);
         if (e != hipSuccess) return e;
       }
     }
@@ -778,7 +793,7 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(s, nsplit));
   }
   const dim3 grid((unsigned)(split_entries(split, grid_items(s, tile)) * s.hq));
-  e = launch_timed(K_FWD, hs, [&] { (void)q_kernels(l.sh).fwd[s.d == 128](&a, grid, hs); });
+  e = launch_timed(K_FWD, hs, [&] { (void)kernels(l.sh).fwd[s.d == 128](&a, grid, hs); });
   if (e != hipSuccess) return hip_fail(e, "fwd_kernel launch");
   if (nsplit > 1) {
     const size_t threads = (size_t)s.T * s.hq * (s.d / 8);
@@ -884,13 +899,11 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   }
   // dQ first: it also writes D = rowsum(dO * O), which dK/dV reads
   const dim3 gq((unsigned)(split_entries(split_q, grid_items(s, qtile)) * s.hq));
-  e = launch_timed(K_DQ, hs, [&] { (void)q_kernels(lq.sh).dq[s.d == 128](&a, gq, hs); });
+  e = launch_timed(K_DQ, hs, [&] { (void)kernels(lq.sh).dq[s.d == 128](&a, gq, hs); });
   if (e != hipSuccess) return hip_fail(e, "bwd_dq_kernel launch");
   if (sk.T > 0) {
     const dim3 gkv((unsigned)(split_entries(split_kv, grid_items(sk, kvtile)) * s.hkv));
-    e = launch_timed(K_DKDV, hs, [&] {
-      (void)kDkdvKernels[lk.sh.groups - 1][s.d == 128](&a, gkv, hs);
-    });
+    e = launch_timed(K_DKDV, hs, [&] { (void)kernels(lk.sh).dkdv[s.d == 128](&a, gkv, hs); });
     if (e != hipSuccess) return hip_fail(e, "bwd_dkdv_kernel launch");
   }
   // the parts' partial gradients (dQ, dK, dV), summed in one launch

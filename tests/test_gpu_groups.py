@@ -30,6 +30,19 @@ def test_groups_full_parity(lengths, hq, hkv, d, causal):
     _full_parity(lengths, hq, hkv, d, causal)
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d,causal", [
+    # short segments that fill the chip: 4-wave dK/dV workgroups of 128 keys
+    ([127, 128, 129, 1, 0, 257, 33, 31] * 4, 24, 12, 128, True),
+    ([127, 128, 129, 1, 0, 257, 33, 31] * 4, 16, 16, 64, False),
+    ([1, 2, 3, 32, 64, 65] * 6, 64, 16, 128, False),
+])
+def test_short_segments_full_parity(lengths, hq, hkv, d, causal):
+    # (the launch counts its items by this bound)
+    per_head = min(sum(lengths) // 128 + len(lengths), len(lengths) * -(-max(lengths) // 128))
+    assert per_head * hkv >= 512
+    _full_parity(lengths, hq, hkv, d, causal)
+
+
 @pytest.mark.parametrize("nseg,hi,hq,d", [
     (2, 4000, 1, 128), (64, 1100, 2, 64), (65, 1100, 2, 64),   # segment-major, to 64 segments
     (63, 500, 2, 128), (128, 500, 1, 64), (129, 500, 1, 64),   # level-major, to 128
