@@ -434,6 +434,18 @@ Launch pick(Which k, const Job& j) {
   const Work w = work_of(k, j, base.sh);
   const int64_t n = w.items * w.heads;
   auto shape = [&](int groups) { return Shape{8, groups}; };
+  // d = 64, causal, a little more than one round of 8-wave query-tile workgroups
+  // (two fit a CU, but the causal ramp leaves the second half-empty): 4-wave
+  // ones, three or four of which fit a CU, even it out.  10,153 tokens x 2/1 heads
+  // (320 workgroups) forward 60 -> 54 us, dQ 73 -> 62; 16,384 x 8 (512) 377 -> 347
+  // and 457 -> 415; 8 x 4,096 x 4 130 -> 137 and 160 -> 146; with 1,024 dQ loses
+  // (1.42 -> 1.50 ms), with 256 both do.
+  if (k != DKDV && j.sq.d == 64 && j.causal && !j.chunk && base.sh.nw == 8 && !base.split.cap) {
+    const int64_t wgs = n * base.split.parts;
+    const Shape four{4, 1};
+    if (wgs > kCUs && wgs < (base.split.parts > 1 ? 2 : 3) * kCUs)
+      return {four, base.split};
+  }
   if (j.sq.N > 1) {
     // Packed batches, dK/dV over 128-key tiles:
     //   * two 4-wave workgroups per CU where segments are short (on average, of

@@ -25,6 +25,8 @@ pytestmark = pytest.mark.gpu
     ([2304], 2, 1, 128, False),       # two groups, uniform parts
     ([300, 1, 129, 512], 2, 1, 64, True),   # packed: dK/dV over 128-key tiles
     ([300, 0, 127], 4, 4, 128, False),
+    ([2305], 30, 15, 64, True),       # d = 64: 300 8-wave tiles, so 4-wave ones
+    ([2100, 65], 30, 30, 64, True),   # the same, packed
 ])
 def test_groups_full_parity(lengths, hq, hkv, d, causal):
     _full_parity(lengths, hq, hkv, d, causal)
