@@ -36,6 +36,7 @@ class PdyError(RuntimeError):
 
 
 _lib = None
+_raw_stream = None
 
 
 def lib() -> ctypes.CDLL:
@@ -120,6 +121,13 @@ def last_error() -> str:
 
 def _stream_handle(device) -> int:
     import torch
+    global _raw_stream
+    if _raw_stream is None:
+        # torch's stream handle without a Stream object around it, where the
+        # installed torch has it (0.1 us instead of 2)
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", False)
+    if _raw_stream and device.index is not None:
+        return _raw_stream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -143,6 +151,8 @@ def validate_cu_seqlens(cu_seqlens, total_tokens: int) -> int:
 
 
 def _check_tensor(t, name, dtype, ndim):
+    if t.dtype == dtype and t.ndim == ndim and t.is_cuda and t.is_contiguous():
+        return
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if t.dim() != ndim:
@@ -169,7 +179,7 @@ def attn_fwd(q, k, v, cu_seqlens, max_seqlen: Optional[int] = None, causal: bool
     _check_tensor(cu_seqlens, "cu_seqlens", torch.int32, 1)
     T, hq, d = q.shape
     hkv = k.shape[1]
-    if tuple(k.shape) != (T, hkv, d) or tuple(v.shape) != (T, hkv, d):
+    if k.shape != (T, hkv, d) or v.shape != (T, hkv, d):
         raise ValueError("k and v must be [T, Hkv, d] with q's T and d")
     if max_seqlen is None:
         max_seqlen = validate_cu_seqlens(cu_seqlens, T)
@@ -180,9 +190,8 @@ def attn_fwd(q, k, v, cu_seqlens, max_seqlen: Optional[int] = None, causal: bool
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((hq, T), dtype=torch.float32, device=q.device)
-    need = fwd_workspace_size(T, n, max_seqlen, hq, hkv, d)
     if workspace is None:
-        workspace = _ws(need, q.device)
+        workspace = _ws(fwd_workspace_size(T, n, max_seqlen, hq, hkv, d), q.device)
     st = lib().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), cu_seqlens.data_ptr(), n, T,
                         int(max_seqlen), hq, hkv, d, int(bool(causal)), float(scale),
                         out.data_ptr(), lse.data_ptr(), workspace.data_ptr(),
@@ -202,9 +211,9 @@ def _bwd_args(q, k, v, o, lse, dout, cu_seqlens, max_seqlen, scale, dq, dk, dv):
     _check_tensor(cu_seqlens, "cu_seqlens", torch.int32, 1)
     T, hq, d = q.shape
     hkv = k.shape[1]
-    if tuple(o.shape) != (T, hq, d) or tuple(dout.shape) != (T, hq, d):
+    if o.shape != (T, hq, d) or dout.shape != (T, hq, d):
         raise ValueError("o and dout must match q")
-    if tuple(lse.shape) != (hq, T):
+    if lse.shape != (hq, T):
         raise ValueError("lse must be [Hq, T]")
     if max_seqlen is None:
         max_seqlen = validate_cu_seqlens(cu_seqlens, T)
@@ -219,7 +228,7 @@ def _bwd_args(q, k, v, o, lse, dout, cu_seqlens, max_seqlen, scale, dq, dk, dv):
     for t, name, shape in ((dq, "dq", (T, hq, d)), (dk, "dk", (T, hkv, d)),
                            (dv, "dv", (T, hkv, d))):
         _check_tensor(t, name, torch.float32, 3)
-        if tuple(t.shape) != shape:
+        if t.shape != shape:
             raise ValueError(f"{name} must be {list(shape)}")
     n = cu_seqlens.numel() - 1
     return T, hq, hkv, d, n, int(max_seqlen), float(scale), dq, dk, dv
@@ -231,9 +240,8 @@ def attn_bwd(q, k, v, o, lse, dout, cu_seqlens, max_seqlen: Optional[int] = None
     """dQ [T, Hq, d], dK, dV [T, Hkv, d] (fp32) of sum(dout * O)."""
     T, hq, hkv, d, n, max_seqlen, scale, dq, dk, dv = _bwd_args(
         q, k, v, o, lse, dout, cu_seqlens, max_seqlen, scale, dq, dk, dv)
-    need = bwd_workspace_size(T, n, max_seqlen, hq, hkv, d)
     if workspace is None:
-        workspace = _ws(need, q.device)
+        workspace = _ws(bwd_workspace_size(T, n, max_seqlen, hq, hkv, d), q.device)
     st = lib().attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
                         dout.data_ptr(), cu_seqlens.data_ptr(), n, T, max_seqlen, hq, hkv, d,
                         int(bool(causal)), scale, dq.data_ptr(), dk.data_ptr(),
