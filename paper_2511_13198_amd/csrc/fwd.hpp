@@ -355,13 +355,13 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
     const uint32_t va = lds_addr(vtile) + v_lane * 2;
     TrRegs vr[2][NDB];  // step T uses vr[T & 1]; no copies of in-flight registers
     // priority while a wave issues these products, as in the backward's product
-    // phases (in the S^T products it is 1.6 % slower) -- with 8 waves, whose wave
-    // w shares a SIMD with wave w + 4, only for the second of the two: it runs
-    // ahead of the first by about a phase, so one's exponentials meet the other's
-    // products more often than when both raise theirs (638,976 tokens x 1 head
-    // 87.35 -> 86.94 ms, packed 65,536 x 32 2.50 -> 2.41; the backward's kernels
-    // lose 1-2 % that way)
-    if (NW == 4 || w >= 4) __builtin_amdgcn_s_setprio(1);
+    // phases (in the S^T products it is 1.6 % slower) -- at d = 128 with 8 waves,
+    // whose wave w shares a SIMD with wave w + 4 alone, only for the second of the
+    // two: it runs ahead of the first by about a phase, so one's exponentials meet
+    // the other's products more often than when both raise theirs (638,976 tokens
+    // x 1 head 87.35 -> 86.94 ms, packed 65,536 x 32 2.50 -> 2.41; the backward's
+    // kernels lose 1-2 % that way, and d = 64, with four waves per SIMD, 3-9 %)
+    if (D == 64 || NW == 4 || w >= 4) __builtin_amdgcn_s_setprio(1);
     static_for<NDB>([&](auto DB) { tr_issue<VL, 0, DB * 32>(va, vr[0][DB]); });
     static_for<NT16>([&](auto T) {
       constexpr int cur = T & 1;
