@@ -359,8 +359,9 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
     // whose wave w shares a SIMD with wave w + 4 alone, only for the second of the
     // two: it runs ahead of the first by about a phase, so one's exponentials meet
     // the other's products more often than when both raise theirs (638,976 tokens
-    // x 1 head 87.35 -> 86.94 ms, packed 65,536 x 32 2.50 -> 2.41; the backward's
-    // kernels lose 1-2 % that way, and d = 64, with four waves per SIMD, 3-9 %)
+    // x 1 head 0.5-0.7 % faster on three cards, e.g. 87.76 -> 87.16 ms; whole steps
+    // change within their noise; the backward's kernels lose 1-2 % that way, and
+    // d = 64, with four waves per SIMD, 3-9 %)
     if (D == 64 || NW == 4 || w >= 4) __builtin_amdgcn_s_setprio(1);
     static_for<NDB>([&](auto DB) { tr_issue<VL, 0, DB * 32>(va, vr[0][DB]); });
     static_for<NT16>([&](auto T) {
