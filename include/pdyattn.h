@@ -193,6 +193,18 @@ pdy_status attn_bwd_noalloc(const void* q, const void* k, const void* v, const v
                             int32_t causal, float scale, float* dq, float* dk, float* dv,
                             void* stream);
 
+/* The launches that a call of these sizes takes, given a workspace of the
+ * size the query above returns: for the forward, dQ and dK/dV kernels in turn
+ * {waves per workgroup, groups of waves that split the inner loop over the same
+ * rows (keys), parts per work item at most}, 9 values (host memory); zeros
+ * where the kernel is not launched.  (A host computation: nothing is launched.) */
+pdy_status pdy_launch_shapes(int32_t total_tokens, int32_t num_seqs, int32_t max_seqlen,
+                             int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                             int32_t causal, int32_t* shapes);
+pdy_status pdy_chunk_launch_shapes(int32_t tq, int32_t tk, int32_t q_offset, int32_t k_offset,
+                                   int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                                   int32_t causal, int32_t* shapes);
+
 /* Static text for a status code. */
 const char* pdy_status_string(int32_t status);
 

@@ -1018,9 +1018,52 @@ pdy_status chunk_sizes(int32_t tq, int32_t tk, int32_t hq, int32_t hkv, int32_t 
   return PDY_OK;
 }
 
+// pdy_launch_shapes for a job; kernels that would not run keep their zeros
+void write_shapes(const Job& j, int32_t* out) {
+  std::fill(out, out + 9, 0);
+  const bool runs[3] = {j.sq.T > 0, j.sq.T > 0, j.sq.T > 0 && j.sk.T > 0};
+  for (int k = 0; k < 3; ++k) {
+    if (!runs[k]) continue;
+    const Launch l = pick((Which)k, j);
+    out[3 * k] = l.sh.nw;
+    out[3 * k + 1] = l.sh.groups;
+    out[3 * k + 2] = l.split.parts;
+  }
+}
+
 }  // namespace
 
 extern "C" {
+
+pdy_status pdy_launch_shapes(int32_t total_tokens, int32_t num_seqs, int32_t max_seqlen,
+                             int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                             int32_t causal, int32_t* shapes) {
+  g_err[0] = 0;
+  Sizes s;
+  pdy_status st;
+  if ((st = check_sizes(total_tokens, num_seqs, max_seqlen, num_heads_q, num_heads_kv, head_dim,
+                        &s)) != PDY_OK)
+    return st;
+  if (causal != 0 && causal != 1) return fail(PDY_ERR_INVALID_ARG, "causal must be 0 or 1");
+  if (shapes == nullptr) return fail(PDY_ERR_INVALID_ARG, "shapes is NULL");
+  write_shapes({s, s, causal, false, 0}, shapes);
+  return PDY_OK;
+}
+
+pdy_status pdy_chunk_launch_shapes(int32_t tq, int32_t tk, int32_t q_offset, int32_t k_offset,
+                                   int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                                   int32_t causal, int32_t* shapes) {
+  g_err[0] = 0;
+  Sizes sq, sk;
+  pdy_status st;
+  if ((st = chunk_sizes(tq, tk, num_heads_q, num_heads_kv, head_dim, &sq, &sk)) != PDY_OK)
+    return st;
+  if (q_offset < 0 || k_offset < 0) return fail(PDY_ERR_INVALID_ARG, "offsets must be >= 0");
+  if (causal != 0 && causal != 1) return fail(PDY_ERR_INVALID_ARG, "causal must be 0 or 1");
+  if (shapes == nullptr) return fail(PDY_ERR_INVALID_ARG, "shapes is NULL");
+  write_shapes({sq, sk, causal, true, q_offset - k_offset}, shapes);
+  return PDY_OK;
+}
 
 pdy_status attn_fwd(const void* q, const void* k, const void* v, const int32_t* cu_seqlens,
                     int32_t num_seqs, int32_t total_tokens, int32_t max_seqlen, int32_t num_heads_q,

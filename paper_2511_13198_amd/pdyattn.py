@@ -25,7 +25,8 @@ PDY_ERR_HIP = -4
 SYMBOLS = ("attn_fwd_workspace_size", "attn_bwd_workspace_size", "attn_fwd", "attn_bwd",
            "attn_fwd_chunk_workspace_size", "attn_bwd_chunk_workspace_size", "attn_fwd_chunk",
            "attn_bwd_chunk", "attn_merge",
-           "attn_validate_cu_seqlens", "attn_bwd_noalloc", "pdy_status_string", "pdy_last_error",
+           "attn_validate_cu_seqlens", "attn_bwd_noalloc", "pdy_launch_shapes",
+           "pdy_chunk_launch_shapes", "pdy_status_string", "pdy_last_error",
            "pdy_kernel_count", "pdy_kernel_name", "pdy_profile_start", "pdy_profile_stop")
 
 
@@ -75,6 +76,10 @@ def lib() -> ctypes.CDLL:
     L.attn_bwd_noalloc.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32,
                                    f32, vp, vp, vp, vp]
     L.attn_bwd_noalloc.restype = i32
+    L.pdy_launch_shapes.argtypes = [i32] * 7 + [ctypes.POINTER(i32)]
+    L.pdy_launch_shapes.restype = i32
+    L.pdy_chunk_launch_shapes.argtypes = [i32] * 8 + [ctypes.POINTER(i32)]
+    L.pdy_chunk_launch_shapes.restype = i32
     L.pdy_status_string.argtypes = [i32]
     L.pdy_status_string.restype = ctypes.c_char_p
     L.pdy_last_error.argtypes = []
@@ -117,6 +122,28 @@ def profile_stop() -> dict:
 
 def last_error() -> str:
     return lib().pdy_last_error().decode()
+
+
+def _shapes(st: int, where: str, out) -> dict:
+    _check(st, where)
+    return {n: tuple(out[3 * i:3 * i + 3])
+            for i, n in enumerate(("fwd_kernel", "bwd_dq_kernel", "bwd_dkdv_kernel"))}
+
+
+def launch_shapes(total_tokens, num_seqs, max_seqlen, hq, hkv, d, causal: bool = True) -> dict:
+    """{kernel name: (waves, groups, parts)} of the launches that attn_fwd and
+    attn_bwd take for these sizes in a workspace of the queried size."""
+    out = (ctypes.c_int32 * 9)()
+    return _shapes(lib().pdy_launch_shapes(total_tokens, num_seqs, max_seqlen, hq, hkv, d,
+                                           int(bool(causal)), out), "pdy_launch_shapes", out)
+
+
+def chunk_launch_shapes(tq, tk, q_offset, k_offset, hq, hkv, d, causal: bool = True) -> dict:
+    """The same for attn_fwd_chunk and attn_bwd_chunk."""
+    out = (ctypes.c_int32 * 9)()
+    return _shapes(lib().pdy_chunk_launch_shapes(tq, tk, q_offset, k_offset, hq, hkv, d,
+                                                 int(bool(causal)), out),
+                   "pdy_chunk_launch_shapes", out)
 
 
 def _stream_handle(device) -> int:

@@ -125,8 +125,28 @@ def test_split_k_workspace():
     assert P.bwd_workspace_size(16384, 1, 16384, 8, 8, 64) < 2 * MiB
     # segments of at most 128 tokens leave nothing to split
     assert P.fwd_workspace_size(1024, 8, 128, 1, 1, 64) < MiB
-    # context-parallel pair calls never split
+    # a context-parallel pair that fills the chip does not split
     assert P.fwd_chunk_workspace_size(8192, 8192, 4, 4, 128) < MiB
+
+
+def test_launch_shapes():
+    """The launches' shapes follow from the sizes (no GPU needed): parts where
+    the size queries count their partial buffers, zeros where nothing runs,
+    and the calls' own argument errors."""
+    s = P.launch_shapes(8192, 1, 8192, 4, 4, 128)
+    assert s["fwd_kernel"][2] > 1 and s["bwd_dkdv_kernel"][2] > 1
+    assert P.launch_shapes(131072, 1, 131072, 4, 4, 128) == {
+        "fwd_kernel": (8, 1, 1), "bwd_dq_kernel": (8, 1, 1), "bwd_dkdv_kernel": (8, 1, 1)}
+    assert set(P.launch_shapes(0, 1, 0, 4, 4, 128).values()) == {(0, 0, 0)}
+    c = P.chunk_launch_shapes(64, 0, 0, 0, 4, 4, 128)
+    assert c["bwd_dkdv_kernel"] == (0, 0, 0) and c["fwd_kernel"][0] > 0
+    for call in (lambda: P.launch_shapes(512, 1, 500, 8, 8, 128),
+                 lambda: P.launch_shapes(512, 1, 512, 8, 8, 96),
+                 lambda: P.chunk_launch_shapes(512, 512, -1, 0, 8, 8, 128)):
+        with pytest.raises(P.PdyError):
+            call()
+    assert P.lib().pdy_launch_shapes(512, 1, 512, 8, 8, 128, 2, None) == P.PDY_ERR_INVALID_ARG
+    assert P.lib().pdy_launch_shapes(512, 1, 512, 8, 8, 128, 1, None) == P.PDY_ERR_INVALID_ARG
 
 
 def test_status_strings_and_kernel_names():

@@ -1,7 +1,8 @@
 """Key groups (forward, dQ) and query groups (dK/dV): workgroups of small
 launches whose waves share the rows (keys) and split the inner loop, combined in
 LDS.  Every element against the fp64 oracle at the sizes where the groups begin,
-end or leave waves without work; the same results from a workspace that only
+end or leave waves without work, each case with the shapes that it is there for
+(waves, groups, parts); the same results from a workspace that only
 holds the launch without groups and parts."""
 import numpy as np
 import pytest
@@ -15,20 +16,43 @@ from tests.test_gpu_parity import _full_parity
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lengths,hq,hkv,d,causal", [
-    ([1], 1, 1, 64, True),            # one row, one key: 3 of 4 groups see nothing
-    ([65], 3, 1, 128, True),          # a 64-row tile and one row
-    ([512], 8, 8, 64, True),          # four groups, unsplit
-    ([511], 2, 2, 128, False),
-    ([2049], 1, 1, 128, True),        # two groups, balanced parts, one row in the last tile
-    ([2500], 6, 2, 64, True),         # three query heads per key head
-    ([2304], 2, 1, 128, False),       # two groups, uniform parts
-    ([300, 1, 129, 512], 2, 1, 64, True),   # packed: dK/dV over 128-key tiles
-    ([300, 0, 127], 4, 4, 128, False),
-    ([2305], 30, 15, 64, True),       # d = 64: 300 8-wave tiles, so 4-wave ones
-    ([2100, 65], 30, 30, 64, True),   # the same, packed
-])
-def test_groups_full_parity(lengths, hq, hkv, d, causal):
+def _shapes(lengths, hq, hkv, d, causal):
+    """(waves, groups, parts) of the forward, dQ and dK/dV launches."""
+    from paper_2511_13198_amd import pdyattn
+    got = pdyattn.launch_shapes(sum(lengths), len(lengths), max(lengths), hq, hkv, d, causal)
+    return [got[n] for n in ("fwd_kernel", "bwd_dq_kernel", "bwd_dkdv_kernel")]
+
+
+# (lengths, hq, hkv, d, causal, the launches' shapes)
+GROUP_CASES = [
+    # one row, one key: 3 of 4 groups see nothing
+    ([1], 1, 1, 64, True, [(8, 4, 1), (8, 4, 1), (8, 2, 1)]),
+    # a 64-row tile and one row
+    ([65], 3, 1, 128, True, [(8, 4, 1), (8, 4, 1), (8, 2, 6)]),
+    # four groups, unsplit
+    ([512], 8, 8, 64, True, [(8, 4, 1), (8, 4, 1), (8, 2, 3)]),
+    ([511], 2, 2, 128, False, [(8, 4, 1), (4, 1, 4), (8, 2, 2)]),
+    # two groups, balanced parts, one row in the last tile
+    ([2049], 1, 1, 128, True, [(8, 2, 9), (8, 2, 9), (8, 2, 11)]),
+    # three query heads per key head
+    ([2500], 6, 2, 64, True, [(8, 2, 3), (8, 2, 3), (8, 2, 11)]),
+    # two groups, uniform parts
+    ([2304], 2, 1, 128, False, [(8, 2, 2), (8, 2, 2), (8, 1, 4)]),
+    # packed: dK/dV over 128-key tiles
+    ([300, 1, 129, 512], 2, 1, 64, True, [(4, 1, 1), (4, 1, 1), (8, 2, 2)]),
+    ([300, 0, 127], 4, 4, 128, False, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
+    # d = 64: 300 8-wave tiles, so a 4-wave forward
+    ([2305], 30, 15, 64, True, [(4, 1, 1), (8, 2, 1), (8, 2, 2)]),
+    # the same, packed: 4-wave forward and dQ
+    ([2100, 65], 30, 30, 64, True, [(4, 1, 1), (4, 1, 1), (8, 1, 1)]),
+    # 4-wave query tiles in uniform parts
+    ([10153], 2, 1, 64, True, [(4, 1, 4), (4, 1, 4), (8, 1, 12)]),
+]
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,causal,shapes", GROUP_CASES)
+def test_groups_full_parity(lengths, hq, hkv, d, causal, shapes):
+    assert _shapes(lengths, hq, hkv, d, causal) == shapes
     _full_parity(lengths, hq, hkv, d, causal)
 
 
@@ -39,9 +63,7 @@ def test_groups_full_parity(lengths, hq, hkv, d, causal):
     ([1, 2, 3, 32, 64, 65] * 6, 64, 16, 128, False),
 ])
 def test_short_segments_full_parity(lengths, hq, hkv, d, causal):
-    # (the launch counts its items by this bound)
-    per_head = min(sum(lengths) // 128 + len(lengths), len(lengths) * -(-max(lengths) // 128))
-    assert per_head * hkv >= 512
+    assert _shapes(lengths, hq, hkv, d, causal) == [(4, 1, 1)] * 3
     _full_parity(lengths, hq, hkv, d, causal)
 
 
@@ -68,21 +90,23 @@ def test_packed_placement(nseg, hi, hq, d):
 
 
 PAIRS = [
-    # (T, hq, hkv, d, causal, (qa, qb), (ka, kb)); the diagonal, an earlier, a
-    # later and an overlapping key chunk, ragged ends, over and under 2,048 rows
-    (4700, 1, 1, 128, True, (2400, 4700), (0, 2399)),
-    (2305, 1, 1, 128, True, (0, 2305), (0, 2305)),
-    (4600, 2, 1, 64, True, (2300, 4600), (2300, 4600)),
-    (3000, 1, 1, 128, True, (100, 2500), (1700, 3000)),
-    (900, 3, 1, 128, True, (200, 765), (0, 566)),
-    (1300, 2, 2, 64, False, (0, 1), (1, 1300)),
-    (2700, 1, 1, 64, True, (0, 300), (300, 2700)),   # nothing visible
-    (10000, 4, 4, 128, True, (8192, 8256), (0, 8192)),
+    # (T, hq, hkv, d, causal, (qa, qb), (ka, kb), shapes); the diagonal, an
+    # earlier, a later and an overlapping key chunk, ragged ends, over and under
+    # 2,048 rows
+    (4700, 1, 1, 128, True, (2400, 4700), (0, 2399), [(8, 2, 4)] * 3),
+    (2305, 1, 1, 128, True, (0, 2305), (0, 2305), [(8, 2, 4)] * 3),
+    (4600, 2, 1, 64, True, (2300, 4600), (2300, 4600), [(8, 2, 4)] * 3),
+    (3000, 1, 1, 128, True, (100, 2500), (1700, 3000), [(8, 2, 2), (8, 2, 2), (8, 2, 4)]),
+    (900, 3, 1, 128, True, (200, 765), (0, 566), [(8, 4, 1), (8, 4, 1), (8, 2, 4)]),
+    (1300, 2, 2, 64, False, (0, 1), (1, 1300), [(8, 2, 2), (8, 2, 2), (8, 2, 1)]),
+    # nothing visible
+    (2700, 1, 1, 64, True, (0, 300), (300, 2700), [(8, 2, 4), (8, 2, 4), (8, 1, 1)]),
+    (10000, 4, 4, 128, True, (8192, 8256), (0, 8192), [(8, 2, 4), (8, 2, 4), (8, 2, 1)]),
 ]
 
 
-@pytest.mark.parametrize("T,hq,hkv,d,causal,qs,ks", PAIRS)
-def test_group_pairs(T, hq, hkv, d, causal, qs, ks):
+@pytest.mark.parametrize("T,hq,hkv,d,causal,qs,ks,shapes", PAIRS)
+def test_group_pairs(T, hq, hkv, d, causal, qs, ks, shapes):
     """Partial forward, the pair's gradients, and both again from the smallest
     accepted workspace and added to what the gradients hold."""
     import torch
@@ -91,6 +115,8 @@ def test_group_pairs(T, hq, hkv, d, causal, qs, ks):
     scale = 1.0 / np.sqrt(d)
     (qa, qb), (ka, kb) = qs, ks
     tq, tk = qb - qa, kb - ka
+    got = pdyattn.chunk_launch_shapes(tq, tk, qa, ka, hq, hkv, d, causal)
+    assert [got[n] for n in ("fwd_kernel", "bwd_dq_kernel", "bwd_dkdv_kernel")] == shapes
     log(f"  T={T} chunk q[{qa},{qb}) k[{ka},{kb}) Hq={hq} Hkv={hkv} d={d} causal={causal}")
     o_ref, l_ref = ora.partial_forward(f["q"][qa:qb], f["k"][ka:kb], f["v"][ka:kb], qa, ka,
                                        causal, scale)
