@@ -106,9 +106,10 @@ __device__ __forceinline__ constexpr int acc_row_off(int r) { return (r >> 2) * 
 // Epilogue of a forward workgroup's wave: normalise its 32 rows (wrow0 ..) and
 // write O (bf16) and LSE (natural log), or, for a split-K part, the part's fp32
 // O and LSE.  A row that saw no key (possible for a chunk or a part) gets O = 0
-// and LSE = -inf.  m: the base-2 exponent offset; lsum: this lane's partial row
-// sum (the other half of the row's keys is on lane l ^ 32).  smem: the tile
-// buffers, no longer in use by any wave.
+// and LSE = -inf; one with a NaN or +inf logit O = NaN and LSE = -inf, whatever the
+// launch's shape (a part hands it on as LSE = NaN).  m: the base-2 exponent offset;
+// lsum: this lane's partial row sum (the other half of the row's keys is on lane
+// l ^ 32).  smem: the tile buffers, no longer in use by any wave.
 template <int D, int NW>
 __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const f32x16 (&oacc)[D / 32],
                                              float m, float lsum, int wrow0, int seg_hi, int h,
@@ -119,7 +120,8 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const f32x16 (&oa
   const float ltot = lsum + partner32(lsum);
   const bool seen = ltot > 0.f;
   const float inv = seen ? 1.f / ltot : 0.f;
-  const float lse = seen ? (m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
+  const float none = a.split.parts > 1 ? ltot - INFINITY : -INFINITY;  // ltot: 0 or NaN
+  const float lse = seen ? (m + __builtin_log2f(ltot)) * kLn2 : none;
   const bool write_lse = l < 32 && row < seg_hi;
   if (a.split.parts > 1) {
     constexpr int PASS = FwdCfg<D, NW>::F32_PASS;
@@ -136,7 +138,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const f32x16 (&oa
 }
 
 // The same for key groups: the groups' partial O (unnormalised) and their m and
-// row sums meet in LDS, weighted 2^(m_j - max_j m_j).
+// row sums meet in LDS, weighted 2^(m_j - max_j m_j) (a NaN sum makes the row's).
 template <int D, int NW, int KG>
 __device__ __forceinline__ void fwd_epilogue_groups(const FwdArgs& a, const f32x16 (&oacc)[D / 32],
                                                     float m, float lsum, int wrow0, int seg_hi,
@@ -174,7 +176,8 @@ __device__ __forceinline__ void fwd_epilogue_groups(const FwdArgs& a, const f32x
         const float inv = tot > 0.f ? 1.f / tot : 0.f;
 #pragma unroll
         for (int j = 0; j < KG; ++j) w[j] *= inv;
-        lse = tot > 0.f ? (mx + __builtin_log2f(tot)) * kLn2 : -INFINITY;
+        const float none = a.split.parts > 1 ? tot - INFINITY : -INFINITY;  // tot: 0 or NaN
+        lse = tot > 0.f ? (mx + __builtin_log2f(tot)) * kLn2 : none;
       },
       [&](int r, int c, const float (&x)[8]) __attribute__((always_inline)) {
         const int row = wrow0 + r;
@@ -528,8 +531,9 @@ __global__ void __launch_bounds__(256) merge_kernel(const uint16_t* oa, const fl
 // merge_kernel:
 //   LSE = log sum_p exp(LSE_p),  O = sum_p exp(LSE_p - LSE) O_p,
 // parts with LSE = -inf weigh nothing and a row where every part is -inf
-// gets O = 0, LSE = -inf.  Parts are fp32, O is rounded to bf16 once.  One
-// 8-element slice of a row and head per thread.
+// gets O = 0, LSE = -inf; a part with LSE = NaN (a NaN or +inf logit) makes the
+// row O = NaN, LSE = -inf, as an unsplit launch does.  Parts are fp32, O is
+// rounded to bf16 once.  One 8-element slice of a row and head per thread.
 template <int D>
 __global__ void __launch_bounds__(256) split_merge_kernel(const float* part_o,
                                                           const float* part_lse, Split sp,
@@ -546,10 +550,18 @@ __global__ void __launch_bounds__(256) split_merge_kernel(const float* part_o,
   const size_t li = (size_t)h * total_tokens + row;
   const int nsplit = sp.nparts(sp.item_of((int)row));
   float mx = -INFINITY;
-  for (int p = 0; p < nsplit; ++p) mx = fmaxf(mx, part_lse[p * rows + li]);
+  bool bad = false;
+  for (int p = 0; p < nsplit; ++p) {
+    const float x = part_lse[p * rows + li];
+    bad |= x != x;
+    mx = fmaxf(mx, x);
+  }
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float tot = 0.f;
-  if (mx != -INFINITY) {
+  if (bad) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = NAN;
+  } else if (mx != -INFINITY) {
     for (int p = 0; p < nsplit; ++p) {
       const float w = __expf(part_lse[p * rows + li] - mx);
       tot += w;

@@ -152,6 +152,63 @@ def test_group_pairs(T, hq, hkv, d, causal, qs, ks, shapes):
                 check_close(nm, got, r)
 
 
+@pytest.mark.parametrize("value", [float("nan"), 3e38, -3e38])
+@pytest.mark.parametrize("T,hq,hkv,d,causal,chunk,shape", [
+    (300, 4, 4, 128, True, None, (8, 4, 1)),
+    (512, 8, 8, 64, True, None, (8, 4, 1)),
+    (2049, 1, 1, 128, True, None, (8, 2, 9)),     # two groups, balanced parts
+    (511, 2, 2, 128, False, None, (8, 4, 1)),
+    (700, 1, 1, 64, False, None, (8, 4, 1)),
+    (2304, 2, 1, 128, False, None, (8, 2, 2)),    # two groups, uniform parts
+    (2600, 6, 6, 64, True, None, (4, 1, 4)),      # one group, parts
+    (2100, 30, 30, 64, True, None, (4, 1, 1)),    # one group, no parts
+    (2305, 1, 1, 128, True, (2305, 2305), (8, 2, 4)),
+    (565, 3, 1, 128, True, (565, 565), (8, 4, 1)),
+])
+def test_nonfinite_logits(value, T, hq, hkv, d, causal, chunk, shape):
+    """One key of NaN, or one whose logits overflow (queries made positive), seen
+    by one part or group of a row only: a row that sees a NaN or +inf logit has
+    O = NaN and LSE = -inf in every launch shape, a key of -inf logits weighs
+    nothing, and the rows before it are untouched."""
+    import torch
+    from paper_2511_13198_amd import pdyattn
+    name = "fwd_kernel"
+    got = (pdyattn.chunk_launch_shapes(T, T, 0, 0, hq, hkv, d, causal) if chunk else
+           pdyattn.launch_shapes(T, 1, T, hq, hkv, d, causal))[name]
+    assert got == shape
+    bits, f = _host(T, hq, hkv, d, 29)
+    j, scale = T // 3, 1.0 / np.sqrt(d)
+    f["q"] = np.abs(f["q"])
+    kd = torch.from_numpy(f["k"]).to(torch.bfloat16)
+    kd[j] = value
+    q = _dev(bits, "q", 0, T).abs()
+    k, v = kd.cuda(), _dev(bits, "v", 0, T)
+    o = torch.zeros_like(q)
+    lse = torch.zeros((hq, T), dtype=torch.float32, device="cuda")
+    if chunk:
+        pdyattn.attn_fwd_chunk(q, k, v, 0, 0, causal, scale, out=o, lse=lse)
+    else:
+        cu = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+        pdyattn.attn_fwd(q, k, v, cu, T, causal, scale, out=o, lse=lse)
+    torch.cuda.synchronize()
+    keep = np.arange(T) != j
+    if value < 0:  # as if the key were not there (row j sees the keys before it)
+        cut = {n: f[n][keep] for n in ("k", "v")}
+        ro, rl = ora.partial_forward(f["q"][:j], cut["k"], cut["v"], 0, 0, causal, scale)
+        # a later row i sees the kept keys 0 .. i - 1
+        so, sl = ora.partial_forward(f["q"][j:], cut["k"], cut["v"], j - 1, 0, causal, scale)
+        check_close("O", o.double().cpu().numpy(), np.concatenate([ro, so]))
+        check_close("LSE", lse.cpu().numpy(), np.concatenate([rl, sl], axis=1))
+        return
+    first = j if causal else 0
+    assert torch.isnan(o[first:]).all()
+    assert torch.isneginf(lse[:, first:]).all()
+    if first:
+        ro, rl = ora.partial_forward(f["q"][:j], f["k"][:j], f["v"][:j], 0, 0, causal, scale)
+        check_close("O", o[:j].double().cpu().numpy(), ro)
+        check_close("LSE", lse[:, :j].cpu().numpy(), rl)
+
+
 def test_underfilled_pairs_split():
     """A pair whose workgroups fill less than half the chip takes partial
     results; one that fills it, and any pair in a small workspace, does not."""
