@@ -453,8 +453,17 @@ Launch pick(Which k, const Job& j) {
     //     190 -> 146 us, 420 of 16-119, 24/8 heads 192 -> 121, 70 of 16-107, 16
     //     heads of 64 21.8 -> 18.7; 32 or 64 equal ones of 512 unchanged, of 1,024
     //     0-15 % slower;
-    //   * two query groups where 256-key tiles leave CUs idle (4,096 tokens in 8
-    //     segments, 16/4 heads of 64: 47.6 -> 37.4 us).
+    //   * two query groups where 256-key tiles leave CUs idle.  Unsplit launches
+    //     (53 random ones 1.20x, none slower): only while the 128-key workgroups
+    //     fit one round and have a few steps each: one head, causal, 32 of 1,024
+    //     tokens 51.5 -> 37.9 us (d = 64: 38.5 -> 29.8), 64 of 512 33.7 -> 29.3; but
+    //     60 of 1,024 56 -> 74 (d = 64: 40 -> 56), 100 of 512 37 -> 41, 30 of 2,048
+    //     without a mask 131 -> 142, 10 of up to 154 x 16 18 -> 22.  Two parts:
+    //     always, without parts (47 random ones 1.27x): 16 of 2,048 74.8 -> 60.2,
+    //     15 of 4,096 247 -> 222.  Four parts, with half as many: at d = 128 with
+    //     at most two query heads a key head, over a quarter to 7/8 of a round (21
+    //     random ones 1.08x); elsewhere the products' lower rate outweighs it (d =
+    //     64: 70 random ones 0.99x, as low as 0.85; 3 of 16,384 297 -> 315).
     if (k != DKDV) return base;
     const Shape four{4, 1};
     if (j.sk.maxlen <= kShortSeg && j.sk.T <= kAverageShort * j.sk.N &&
@@ -462,7 +471,13 @@ Launch pick(Which k, const Job& j) {
       return {four, uniform_split(1)};
     if (n >= kCUs) return base;
     const Work w2 = work_of(k, j, shape(2));
-    return {shape(2), split_of(w2, j, std::max(1, base.split.parts / 2))};
+    const int64_t n2 = w2.items * w2.heads;
+    const int p = base.split.parts;
+    if (p == 1 ? n2 > kCUs || w.inner < 4
+               : p > 2 && (j.sq.d == 64 || j.sq.hq > 2 * j.sq.hkv || n2 < kCUs / 4 ||
+                           n2 > kCUs * 7 / 8))
+      return base;
+    return {shape(2), split_of(w2, j, std::max(1, p / 2))};
   }
   if (base.split.parts > 1) {
     // Two groups of half as many parts: as many workgroups and half the partial

@@ -39,7 +39,9 @@ GROUP_CASES = [
     # two groups, uniform parts
     ([2304], 2, 1, 128, False, [(8, 2, 2), (8, 2, 2), (8, 1, 4)]),
     # packed: dK/dV over 128-key tiles
-    ([300, 1, 129, 512], 2, 1, 64, True, [(4, 1, 1), (4, 1, 1), (8, 2, 2)]),
+    ([600, 1, 129, 1024] * 4, 3, 3, 128, True, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
+    ([2048, 1000, 2000], 4, 2, 128, True, [(4, 1, 2), (4, 1, 2), (8, 2, 2)]),
+    ([300, 1, 129, 512], 2, 1, 64, True, [(4, 1, 1), (4, 1, 1), (8, 1, 4)]),
     ([300, 0, 127], 4, 4, 128, False, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
     # d = 64: 300 8-wave tiles, so a 4-wave forward
     ([2305], 30, 15, 64, True, [(4, 1, 1), (8, 2, 1), (8, 2, 2)]),

@@ -1,0 +1,34 @@
+"""Which launches the sizes choose, on both sides of the lines that were measured
+(no GPU needed: the choice is a host computation)."""
+import pytest
+
+from paper_2511_13198_amd import pdyattn as P
+
+
+def shapes(lengths, hq, hkv, d, causal):
+    return P.launch_shapes(sum(lengths), len(lengths), max(lengths), hq, hkv, d, causal)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,causal,expect", [
+    # unsplit, 256-key tiles on part of the chip: two query groups only while
+    # their 128-key workgroups fit one round and have a few steps
+    ([512] * 64, 1, 1, 128, True, (8, 2, 1)),
+    ([1024] * 32, 1, 1, 64, False, (8, 2, 1)),
+    ([1024] * 33, 1, 1, 64, False, (8, 1, 1)),
+    ([1024] * 60, 1, 1, 128, True, (8, 1, 1)),
+    ([512] * 100, 1, 1, 128, False, (8, 1, 1)),
+    ([2048] * 30, 1, 1, 128, False, (8, 1, 1)),
+    ([192] * 8, 2, 2, 128, True, (8, 1, 1)),
+    # two parts: two groups without parts
+    ([2048] * 16, 1, 1, 64, True, (8, 2, 1)),
+    ([4096] * 15, 1, 1, 128, False, (8, 2, 1)),
+    # four parts: at d = 128, on both sides of the lines
+    ([2048] * 4, 2, 2, 128, True, (8, 2, 2)),
+    ([2048] * 4, 8, 2, 128, True, (8, 1, 4)),
+    ([2048] * 4, 2, 2, 64, True, (8, 1, 4)),
+    ([2048] * 3, 1, 1, 128, True, (8, 1, 4)),
+    ([4096] * 8, 1, 1, 128, True, (8, 1, 4)),
+    ([16384] * 3, 1, 1, 64, True, (8, 1, 4)),
+])
+def test_packed_dkdv_groups(lengths, hq, hkv, d, causal, expect):
+    assert shapes(lengths, hq, hkv, d, causal)["bwd_dkdv_kernel"] == expect
