@@ -438,13 +438,18 @@ Launch pick(Which k, const Job& j) {
   // (two fit a CU, but the causal ramp leaves the second half-empty): 4-wave
   // ones, three or four of which fit a CU, even it out.  10,153 tokens x 2/1 heads
   // (320 workgroups) forward 60 -> 54 us, dQ 73 -> 62; 16,384 x 8 (512) 377 -> 347
-  // and 457 -> 415; 8 x 4,096 x 4 130 -> 137 and 160 -> 146; with 1,024 dQ loses
-  // (1.42 -> 1.50 ms), with 256 both do.
+  // and 457 -> 415; with 1,024 dQ loses (1.42 -> 1.50 ms), with 256 both do.
+  // Packed batches (150 random ones each): with six heads or more forward 1.10x,
+  // dQ 1.06x, 2 of 106 slower (by 4-5 %); with fewer, whose K/V the eight L2s
+  // share, the tiles' second copy of K and V costs up to 14 % of a launch in parts
+  // or of more than 448 workgroups (8 x 4,096 x 4 heads forward 130 -> 134 us, 5 x
+  // 8,192 x 4 dQ 308 -> 322), while smaller unsplit ones gain (37, 1.0-1.31x).
   if (k != DKDV && j.sq.d == 64 && j.causal && !j.chunk && base.sh.nw == 8 && !base.split.cap) {
-    const int64_t wgs = n * base.split.parts;
+    const int parts = base.split.parts;
+    const int64_t wgs = n * parts;
     const Shape four{4, 1};
-    if (wgs > kCUs && wgs < (base.split.parts > 1 ? 2 : 3) * kCUs)
-      return {four, base.split};
+    const bool evens = j.sq.N == 1 || j.sq.hq >= 6 || (parts == 1 && wgs <= kCUs * 7 / 4);
+    if (evens && wgs > kCUs && wgs < (parts > 1 ? 2 : 3) * kCUs) return {four, base.split};
   }
   if (j.sq.N > 1) {
     // Packed batches, dK/dV over 128-key tiles:
@@ -507,8 +512,9 @@ Launch pick(Which k, const Job& j) {
     // (by its sizes alone: its workspace query knows no offsets).  A
     // device's pairs of a zig-zag ring of 8 over 32,768 tokens x 4 heads (2,048
     // rows each): forward 0.78 -> 0.62 ms, backward 2.75 -> 1.52; over 131,072
-    // (8,192 rows, groups without a split) 2.45 -> 2.50 on two streams, which
-    // two launches without groups just fill, and 9.76 -> 7.81.
+    // (8,192 rows, groups without a split) forward 2.24-2.40 -> 2.35-2.37 on two
+    // streams, which two launches without groups just fill (2.19-2.35), backward
+    // 9.69 -> 7.29; a pair alone 183 -> 105 us.
     const Work w2 = work_of(k, j, shape(2));
     int p = 1;
     while (p < kMaxSplit && w2.items * w2.heads * p * 2 <= kCUs && w2.inner >= 8 * p) p *= 2;

@@ -32,3 +32,20 @@ def shapes(lengths, hq, hkv, d, causal):
 ])
 def test_packed_dkdv_groups(lengths, hq, hkv, d, causal, expect):
     assert shapes(lengths, hq, hkv, d, causal)["bwd_dkdv_kernel"] == expect
+
+
+@pytest.mark.parametrize("lengths,hq,fwd,dq", [
+    # few heads: 4-wave query tiles only in unsplit launches up to 448 workgroups
+    ([4096] * 8, 4, (8, 1, 1), (8, 1, 1)),       # 512
+    ([4096] * 7, 4, (4, 1, 1), (8, 1, 2)),       # 448; dQ in parts
+    ([8192] * 5, 4, (8, 1, 1), (8, 1, 1)),       # 640
+    ([7697, 6000, 5554, 4800], 4, (8, 1, 2), (8, 1, 2)),
+    # six heads or more: up to 767
+    ([4096] * 7, 6, (4, 1, 1), (4, 1, 1)),       # 672
+    ([4096] * 6, 8, (8, 1, 1), (8, 1, 1)),       # 768
+    # a single sequence's line stays
+    ([16384], 8, (4, 1, 1), (4, 1, 1)),
+])
+def test_d64_four_wave_query_tiles(lengths, hq, fwd, dq):
+    got = shapes(lengths, hq, hq, 64, True)
+    assert (got["fwd_kernel"], got["bwd_dq_kernel"]) == (fwd, dq)
