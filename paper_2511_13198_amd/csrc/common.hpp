@@ -539,19 +539,27 @@ struct Plan {
 // always gets the lightest block; with 8 heads this is the plain order).
 // Measured at 131,072 tokens: dK/dV with 1 kv head -4.7 %, 2 kv heads
 // -3.9 %, 4 kv heads -0.3 to -0.8 %; forward and dQ with 4 query heads
-// -1.4 % and -0.6 %.  Other head counts keep the plain order.  A bijection
-// on [0, n); the last partial round keeps the plain order.
+// -1.4 % and -0.6 %.  The last, partial round is dealt in the same blocks: in the
+// plain order its heavy and light entries met the first round's unevenly (16,200
+// tokens x 4 heads over 508 workgroups: forward 308 -> 267 us, dQ 406 -> 360,
+// dK/dV 553 -> 487).  Other head counts and launches of less than a round
+// keep the plain order.  A bijection on [0, n).
 __device__ __forceinline__ void xcd_order(int b, int n, int nheads, int& head, int& entry) {
   constexpr int kXcd = 8, kPer = 32, kRound = kXcd * kPer;
   head = b % nheads;
   entry = b / nheads;
-  if (kXcd % nheads != 0 || b >= n / kRound * kRound) return;
+  if (kXcd % nheads != 0 || n < kRound) return;
   const int g = kXcd / nheads;          // XCDs per head
   const int sub = (b % kXcd) / nheads;  // which of them
   const int s = b / kXcd;               // workgroup index on this XCD
   const int r = s / kPer, q = s % kPer;
-  const int blk = (r & 1) ? g - 1 - sub : sub;
-  entry = (r * g + blk) * kPer + q;
+  // the head's entries of this round, dealt to its XCDs one by one: XCD i has
+  // per + (i < more) of them
+  const int mine = min(n / nheads - r * g * kPer, g * kPer);
+  const int per = mine / g, more = mine % g;
+  const int first = (r & 1) ? mine - (sub + 1) * per - min(sub + 1, more)
+                            : sub * per + min(sub, more);
+  entry = r * g * kPer + first + q;
 }
 
 // Split-K of a launch whose work items cannot fill the chip: each item's

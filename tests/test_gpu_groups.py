@@ -91,6 +91,31 @@ def test_packed_placement(nseg, hi, hq, d):
     assert ran == (nseg in (65, 129))
 
 
+@pytest.mark.parametrize("nseg,hq,hkv,d,causal", [
+    (300, 1, 1, 128, True),   # 44 workgroups over the 8 XCDs of one head
+    (131, 2, 2, 64, False),   # 3 of each of two heads over 4 XCDs
+    (67, 4, 4, 64, True),     # 3 of each of four heads over 2 XCDs
+    (33, 8, 4, 128, True),    # one of each of eight heads
+    (200, 3, 3, 64, True),    # heads that do not divide the XCDs
+])
+def test_last_partial_round(nseg, hq, hkv, d, causal):
+    """One workgroup per segment and head, a full round and a ragged rest: every
+    item has its place (one left out keeps the NaN it was given, one of
+    accumulating launches taken twice would not match)."""
+    assert nseg * hq > 256 and nseg * hq % 256
+    _full_parity([64 + (i * 7) % 60 for i in range(nseg)], hq, hkv, d, causal)
+
+
+def test_last_partial_round_single():
+    """127 key and query tiles of 128 over two XCDs per head: the second round
+    is four workgroups short."""
+    from tests.test_gpu_parity import _sampled_parity
+    w = wl.Workload("single16200_h4", [16200], 4, 4, 128)
+    assert _shapes([16200], 4, 4, 128, True) == [(8, 2, 1)] * 3
+    _sampled_parity(w, device_gen=True, heads=[0, 3], kv_heads=[1, 2], per_seg_random=48,
+                    tail_cols=128)
+
+
 PAIRS = [
     # (T, hq, hkv, d, causal, (qa, qb), (ka, kb), shapes); the diagonal, an
     # earlier, a later and an overlapping key chunk, ragged ends, over and under
