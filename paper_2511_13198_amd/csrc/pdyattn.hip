@@ -600,18 +600,26 @@ size_t bwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
 constexpr int kSegMajorTiles = 8;
 bool seg_major(const Sizes& s, int tile) { return tiles_of(s, tile) >= kSegMajorTiles; }
 
-// Whether plan_kernel builds a schedule (few segments: the workgroups place
-// their items themselves).
-bool needs_plan(const Sizes& s, int tile) {
-  return s.N > (seg_major(s, tile) ? pdy::kDirectSegMajor : 64 * pdy::kDirectChunks);
+// Whether plan_kernel builds a schedule for `heads` heads, or the workgroups
+// place their items themselves: batches of few segments, in the segment-major
+// order (a pass over the segments in every wave) also only up to kDirectWork
+// segments x workgroups.  Forward, 4/4 heads: 16 segments of about 2,000 tokens
+// (8,192) 5 us less than with a schedule, 32 (34,000) 5 us more, 48 of d = 64
+// (77,000) 153 against 140; 32/8 heads of 64, 64 of about 1,000 (1.1 million) 475
+// against 396 us.  The level-major order's ballots stay ahead throughout.
+constexpr int64_t kDirectWork = 16384;
+bool needs_plan(const Sizes& s, int tile, int64_t heads) {
+  if (s.N == 1) return false;
+  if (!seg_major(s, tile)) return s.N > 64 * pdy::kDirectChunks;
+  return s.N > pdy::kDirectSegMajor || s.N * grid_items(s, tile) * heads > kDirectWork;
 }
 
-pdy::Plan make_plan(const int32_t* cu, int32_t* ws, const Sizes& s, int tile) {
+pdy::Plan make_plan(const int32_t* cu, int32_t* ws, const Sizes& s, int tile, int64_t heads) {
   const int nt = tiles_of(s, tile);
   pdy::Plan p;
   p.cu = cu;
   p.n = (int32_t)s.N;
-  p.direct = !needs_plan(s, tile);
+  p.direct = !needs_plan(s, tile, heads);
   p.tile_log2 = __builtin_ctz((unsigned)tile);  // every shape's tile is a power of two
   p.max_nt = nt;
   p.seg_major = seg_major(s, tile);
@@ -798,7 +806,7 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   int32_t* ws = reinterpret_cast<int32_t*>(workspace);
-  if (needs_plan(s, tile) &&
+  if (needs_plan(s, tile, s.hq) &&
       (st = launch_plans(plan_job(cu, ws, s, tile), nullptr, hs)) != PDY_OK)
     return st;
 
@@ -808,7 +816,7 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   a.v = static_cast<const uint16_t*>(v);
   a.o = static_cast<uint16_t*>(o);
   a.lse = lse;
-  a.plan = make_plan(cu, ws, s, tile);
+  a.plan = make_plan(cu, ws, s, tile, s.hq);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
   a.hkv = (int)s.hkv;
@@ -889,7 +897,7 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     // (packed batches: both sides have the same segments)
     const pdy::PlanJob q_job = plan_job(cu, ws_q, s, qtile);
     const pdy::PlanJob kv_job = plan_job(cu, ws, sk, kvtile);
-    const bool need_q = needs_plan(s, qtile), need_kv = needs_plan(sk, kvtile);
+    const bool need_q = needs_plan(s, qtile, s.hq), need_kv = needs_plan(sk, kvtile, sk.hkv);
     if (need_q || need_kv) {
       st = launch_plans(need_q ? q_job : kv_job, need_q && need_kv ? &kv_job : nullptr, hs);
       if (st != PDY_OK) return st;
@@ -906,8 +914,8 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   a.dq = dq;
   a.dk = dk;
   a.dv = dv;
-  a.plan = make_plan(cu, ws, sk, kvtile);
-  a.plan_q = make_plan(cu, ws_q, s, qtile);
+  a.plan = make_plan(cu, ws, sk, kvtile, sk.hkv);
+  a.plan_q = make_plan(cu, ws_q, s, qtile, s.hq);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
   a.hkv = (int)s.hkv;

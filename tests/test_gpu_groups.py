@@ -69,18 +69,21 @@ def test_short_segments_full_parity(lengths, hq, hkv, d, causal):
     _full_parity(lengths, hq, hkv, d, causal)
 
 
-@pytest.mark.parametrize("nseg,hi,hq,d", [
-    (2, 4000, 1, 128), (64, 1100, 2, 64), (65, 1100, 2, 64),   # segment-major, to 64 segments
-    (63, 500, 2, 128), (128, 500, 1, 64), (129, 500, 1, 64),   # level-major, to 128
+@pytest.mark.parametrize("nseg,hi,rest,hq,d,scheduled", [
+    # segment-major: to 64 segments and 16,384 segments x workgroups
+    (2, 4000, 4000, 1, 128, False), (64, 1100, 100, 2, 64, False), (65, 1100, 100, 2, 64, True),
+    (64, 1100, 1100, 2, 64, True),
+    # level-major: to 128 segments
+    (63, 500, 500, 2, 128, False), (128, 500, 500, 1, 64, False), (129, 500, 500, 1, 64, True),
 ])
-def test_packed_placement(nseg, hi, hq, d):
-    """Packed batches on both sides of the segment counts up to which the
-    workgroups place their items themselves: every element (an item placed
-    twice, wrongly or not at all shows), equal counts and empty segments among
-    them, and the schedule kernel runs only beyond."""
+def test_packed_placement(nseg, hi, rest, hq, d, scheduled):
+    """Packed batches on both sides of the sizes up to which the workgroups
+    place their items themselves: every element (an item placed twice, wrongly
+    or not at all shows), equal counts and empty segments among them, and the
+    schedule kernel runs only beyond."""
     from paper_2511_13198_amd import pdyattn
     rng = np.random.default_rng(nseg)
-    lengths = [int(x) for x in rng.integers(1, hi + 1, size=nseg)]
+    lengths = [int(x) for x in rng.integers(1, rest + 1, size=nseg)]
     lengths[0] = hi                    # the longest, so that the order is known
     lengths[-1] = 0
     if nseg > 2:
@@ -88,7 +91,7 @@ def test_packed_placement(nseg, hi, hq, d):
     pdyattn.profile_start()
     _full_parity(lengths, hq, hq, d, True)
     ran = "plan_kernel" in pdyattn.profile_stop()
-    assert ran == (nseg in (65, 129))
+    assert ran == scheduled
 
 
 @pytest.mark.parametrize("nseg,hq,hkv,d,causal", [
