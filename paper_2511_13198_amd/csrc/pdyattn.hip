@@ -600,7 +600,7 @@ size_t bwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
 constexpr int kSegMajorTiles = 8;
 bool seg_major(const Sizes& s, int tile) { return tiles_of(s, tile) >= kSegMajorTiles; }
 
-// Whether plan_kernel builds a schedule for `heads` heads, or the workgroups
+// Whether plan_kernel builds a schedule for a launch of `wgs` workgroups, or they
 // place their items themselves: batches of few segments, in the segment-major
 // order (a pass over the segments in every wave) also only up to kDirectWork
 // segments x workgroups.  Forward, 4/4 heads: 16 segments of about 2,000 tokens
@@ -608,18 +608,18 @@ bool seg_major(const Sizes& s, int tile) { return tiles_of(s, tile) >= kSegMajor
 // (77,000) 153 against 140; 32/8 heads of 64, 64 of about 1,000 (1.1 million) 475
 // against 396 us.  The level-major order's ballots stay ahead throughout.
 constexpr int64_t kDirectWork = 16384;
-bool needs_plan(const Sizes& s, int tile, int64_t heads) {
+bool needs_plan(const Sizes& s, int tile, int64_t wgs) {
   if (s.N == 1) return false;
   if (!seg_major(s, tile)) return s.N > 64 * pdy::kDirectChunks;
-  return s.N > pdy::kDirectSegMajor || s.N * grid_items(s, tile) * heads > kDirectWork;
+  return s.N > pdy::kDirectSegMajor || s.N * wgs > kDirectWork;
 }
 
-pdy::Plan make_plan(const int32_t* cu, int32_t* ws, const Sizes& s, int tile, int64_t heads) {
+pdy::Plan make_plan(const int32_t* cu, int32_t* ws, const Sizes& s, int tile, int64_t wgs) {
   const int nt = tiles_of(s, tile);
   pdy::Plan p;
   p.cu = cu;
   p.n = (int32_t)s.N;
-  p.direct = !needs_plan(s, tile, heads);
+  p.direct = !needs_plan(s, tile, wgs);
   p.tile_log2 = __builtin_ctz((unsigned)tile);  // every shape's tile is a power of two
   p.max_nt = nt;
   p.seg_major = seg_major(s, tile);
@@ -806,7 +806,8 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   int32_t* ws = reinterpret_cast<int32_t*>(workspace);
-  if (needs_plan(s, tile, s.hq) &&
+  const int64_t wgs = split_entries(split, grid_items(s, tile)) * s.hq;
+  if (needs_plan(s, tile, wgs) &&
       (st = launch_plans(plan_job(cu, ws, s, tile), nullptr, hs)) != PDY_OK)
     return st;
 
@@ -816,7 +817,7 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   a.v = static_cast<const uint16_t*>(v);
   a.o = static_cast<uint16_t*>(o);
   a.lse = lse;
-  a.plan = make_plan(cu, ws, s, tile, s.hq);
+  a.plan = make_plan(cu, ws, s, tile, wgs);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
   a.hkv = (int)s.hkv;
@@ -833,7 +834,7 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     a.part_o = reinterpret_cast<float*>(w);
     a.part_lse = reinterpret_cast<float*>(w + part_o_bytes(s, nsplit));
   }
-  const dim3 grid((unsigned)(split_entries(split, grid_items(s, tile)) * s.hq));
+  const dim3 grid((unsigned)wgs);
   e = launch_timed(K_FWD, hs, [&] { (void)kernels(l.sh).fwd[s.d == 128](&a, grid, hs); });
   if (e != hipSuccess) return hip_fail(e, "fwd_kernel launch");
   if (nsplit > 1) {
@@ -892,12 +893,14 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   int32_t* ws_q = reinterpret_cast<int32_t*>(wsb + kv_plan_bytes(sk, lk.sh));
   float* dd = reinterpret_cast<float*>(wsb + kv_plan_bytes(sk, lk.sh) + q_plan_bytes(s, lq.sh));
 
+  const int64_t wgs_q = split_entries(split_q, grid_items(s, qtile)) * s.hq;
+  const int64_t wgs_kv = split_entries(split_kv, grid_items(sk, kvtile)) * sk.hkv;
   {
     // the query-tile schedule and the key-tile one, where they are needed
     // (packed batches: both sides have the same segments)
     const pdy::PlanJob q_job = plan_job(cu, ws_q, s, qtile);
     const pdy::PlanJob kv_job = plan_job(cu, ws, sk, kvtile);
-    const bool need_q = needs_plan(s, qtile, s.hq), need_kv = needs_plan(sk, kvtile, sk.hkv);
+    const bool need_q = needs_plan(s, qtile, wgs_q), need_kv = needs_plan(sk, kvtile, wgs_kv);
     if (need_q || need_kv) {
       st = launch_plans(need_q ? q_job : kv_job, need_q && need_kv ? &kv_job : nullptr, hs);
       if (st != PDY_OK) return st;
@@ -914,8 +917,8 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
   a.dq = dq;
   a.dk = dk;
   a.dv = dv;
-  a.plan = make_plan(cu, ws, sk, kvtile, sk.hkv);
-  a.plan_q = make_plan(cu, ws_q, s, qtile, s.hq);
+  a.plan = make_plan(cu, ws, sk, kvtile, wgs_kv);
+  a.plan_q = make_plan(cu, ws_q, s, qtile, wgs_q);
   a.total_tokens = (int)s.T;
   a.hq = (int)s.hq;
   a.hkv = (int)s.hkv;
@@ -939,11 +942,11 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     if (nsplit_q > 1) a.part_dq = reinterpret_cast<float*>(w);
   }
   // dQ first: it also writes D = rowsum(dO * O), which dK/dV reads
-  const dim3 gq((unsigned)(split_entries(split_q, grid_items(s, qtile)) * s.hq));
+  const dim3 gq((unsigned)wgs_q);
   e = launch_timed(K_DQ, hs, [&] { (void)kernels(lq.sh).dq[s.d == 128](&a, gq, hs); });
   if (e != hipSuccess) return hip_fail(e, "bwd_dq_kernel launch");
   if (sk.T > 0) {
-    const dim3 gkv((unsigned)(split_entries(split_kv, grid_items(sk, kvtile)) * s.hkv));
+    const dim3 gkv((unsigned)wgs_kv);
     e = launch_timed(K_DKDV, hs, [&] { (void)kernels(lk.sh).dkdv[s.d == 128](&a, gkv, hs); });
     if (e != hipSuccess) return hip_fail(e, "bwd_dkdv_kernel launch");
   }

@@ -73,6 +73,7 @@ def test_short_segments_full_parity(lengths, hq, hkv, d, causal):
     # segment-major: to 64 segments and 16,384 segments x workgroups
     (2, 4000, 4000, 1, 128, False), (64, 1100, 100, 2, 64, False), (65, 1100, 100, 2, 64, True),
     (64, 1100, 1100, 2, 64, True),
+    (48, 2841, 1300, 1, 64, True),   # within them but for its parts
     # level-major: to 128 segments
     (63, 500, 500, 2, 128, False), (128, 500, 500, 1, 64, False), (129, 500, 500, 1, 64, True),
 ])
