@@ -438,7 +438,9 @@ Launch pick(Which k, const Job& j) {
   // (two fit a CU, but the causal ramp leaves the second half-empty): 4-wave
   // ones, three or four of which fit a CU, even it out.  10,153 tokens x 2/1 heads
   // (320 workgroups) forward 60 -> 54 us, dQ 73 -> 62; 16,384 x 8 (512) 377 -> 347
-  // and 457 -> 415; with 1,024 dQ loses (1.42 -> 1.50 ms), with 256 both do.
+  // and 457 -> 415; with 1,024 dQ loses (1.42 -> 1.50 ms), with 256 both do, and
+  // unsplit dQ from about two rounds on (38,243 x 4, 600 workgroups, 2.6 -> 2.7 ms;
+  // with six heads or more from 2.5).
   // Packed batches (150 random ones each): with six heads or more forward 1.10x,
   // dQ 1.06x, 2 of 106 slower (by 4-5 %); with fewer, whose K/V the eight L2s
   // share, the tiles' second copy of K and V costs up to 14 % of a launch in parts
@@ -448,7 +450,10 @@ Launch pick(Which k, const Job& j) {
     const int parts = base.split.parts;
     const int64_t wgs = n * parts;
     const Shape four{4, 1};
-    const bool evens = j.sq.N == 1 || j.sq.hq >= 6 || (parts == 1 && wgs <= kCUs * 7 / 4);
+    const bool heads = j.sq.hq >= 6;
+    const bool evens =
+        j.sq.N == 1 ? k == FWD || parts > 1 || wgs <= (heads ? kCUs * 5 / 2 : 2 * kCUs)
+                    : heads || (parts == 1 && wgs <= kCUs * 7 / 4);
     if (evens && wgs > kCUs && wgs < (parts > 1 ? 2 : 3) * kCUs) return {four, base.split};
   }
   if (j.sq.N > 1) {
@@ -486,23 +491,35 @@ Launch pick(Which k, const Job& j) {
   }
   if (base.split.parts > 1) {
     // Two groups of half as many parts: as many workgroups and half the partial
-    // results, but products 5-7 % slower (d = 64, whose partial results are half
-    // as large: 10-12 %), so for launches that are not long.  Single sequences of
-    // d = 128, all combining included: 2,500 tokens x 6/2 heads backward 82 -> 73
-    // us, 6,144 x 1 forward 32.7 -> 28.7 and backward 77 -> 69, 8,192 x 4 92 -> 88
-    // and 281 -> 266; 16,384 x 4, no longer split, 288 -> 274 and 880 -> 856;
-    // 10,153 x 2 of d = 64 would lose (67 -> 71 and 156 -> 164).  (Not for the
-    // 4-wave query-tile kernels: no gain.)
+    // results, but slower products, so where what is saved (partial results moved,
+    // and the combining launch where none are left) is at least this share of the
+    // kernel's time.  The shares are those from which on 1,200 random single
+    // sequences, timed both ways, gain on the mean.  d = 128, all combining
+    // included: 2,500 tokens x 6/2 heads backward 82 -> 73 us, 6,144 x 1 forward
+    // 32.7 -> 28.7 and backward 77 -> 69, 8,192 x 4 92 -> 88 and 281 -> 266; below
+    // the line 16,128 x 4 forward 283 -> 294, 16,314 x 2/1 dK/dV 247 -> 297.  d =
+    // 64, whose one-group forward and dQ share a CU by two: 13,433 x 3 forward 101
+    // -> 117 us, 11,282 x 4 97 -> 112; of two parts only where the causal ramp's
+    // two rounds of two-group workgroups pair up (8,192 x 8, forward 113 -> 102,
+    // 8,853 x 8 119 -> 121).  (Not for the 4-wave query-tile
+    // kernels: no gain.)
     if (base.sh.nw == 4) return base;
-    static constexpr double kSlower[2][3] = {{0.12, 0.10, 0.10}, {0.07, 0.05, 0.05}};
+    constexpr double kNever = 1e9;
+    // [d = 64, 128][kernel][two parts, four, balanced]
+    static constexpr double kShare[2][3][3] = {
+        {{0, kNever, 0.12}, {0, kNever, 0.10}, {0.13, 0.25, 0.16}},
+        {{0.11, 0.18, 0.17}, {0.05, 0.08, 0.08}, {0.05, 0.11, 0.05}}};
     constexpr double kMovedBytesPerUs = 5.0e6;
     const int p = split_parts(n, w.inner, w.unit_us, w.slice);
     const double longest = base.split.cap ? base.split.cap : (double)((w.inner + p - 1) / p);
     const double mean = (double)n / kCUs * w.inner * (j.causal ? 0.5 : 1.0);
     const double us = std::max(longest, mean) * w.unit_us;
     const double saved_us = p * w.slice / kMovedBytesPerUs + (p == 2 ? kLaunchUs : 0.0);
-    if (kSlower[j.sq.d == 128][k] * us > saved_us) return base;
+    if (kShare[j.sq.d == 128][k][p == 2 ? 0 : base.split.cap ? 2 : 1] * us > saved_us) return base;
     const Work w2 = work_of(k, j, shape(2));
+    if (p == 2 && j.sq.d == 64 && k != DKDV &&
+        (!j.causal || 10 * w2.items * w2.heads > 21 * kCUs))
+      return base;
     return {shape(2), split_of(w2, j, p / 2)};
   }
   // a 4-wave launch that has a workgroup for every CU is left alone
@@ -514,11 +531,27 @@ Launch pick(Which k, const Job& j) {
     // rows each): forward 0.78 -> 0.62 ms, backward 2.75 -> 1.52; over 131,072
     // (8,192 rows, groups without a split) forward 2.24-2.40 -> 2.35-2.37 on two
     // streams, which two launches without groups just fill (2.19-2.35), backward
-    // 9.69 -> 7.29; a pair alone 183 -> 105 us.
+    // 9.69 -> 7.29; a pair alone 183 -> 105 us.  (Forward and dQ over fewer than
+    // 1,280 keys: no parts, 34 pairs of 768-1,279 keys down to 0.76x.)
     const Work w2 = work_of(k, j, shape(2));
+    const int least = k == DKDV ? 8 : 10;
     int p = 1;
-    while (p < kMaxSplit && w2.items * w2.heads * p * 2 <= kCUs && w2.inner >= 8 * p) p *= 2;
+    while (p < kMaxSplit && w2.items * w2.heads * p * 2 <= kCUs &&
+           w2.inner >= (p == 1 ? least : 8 * p))
+      p *= 2;
     if (p > 1) return {shape(2), split_of(w2, j, p)};
+  }
+  if (k != DKDV) {
+    // Key groups need a few keys each (up to 128 keys 7-15 % slower, from 256 on
+    // faster: 140 random sequences).  Launches of more than a round whose items are
+    // even: two of the d = 64 one-group workgroups share a CU, groups' do not (24
+    // pairs and sequences 0.82-1.00x); nor do they pay for a forward over the
+    // diagonal that is much more than a round (2,901 x 32 causal 77 -> 87 us, a
+    // 13,542-row pair x 8 360 -> 379; up to 320 workgroups 1.03-1.39x).
+    const bool ramp = j.causal && j.shift < j.sk.T / 2;
+    if (j.sk.T < 256) return base;
+    if (j.sq.d == 64 && n > kCUs && !ramp) return base;
+    if (j.sq.d == 128 && k == FWD && n > kCUs * 5 / 4 && ramp) return base;
   }
   Launch best = base;
   double t = 0.97 * est_unsplit_us(k, j, base.sh);

@@ -25,26 +25,32 @@ def _shapes(lengths, hq, hkv, d, causal):
 
 # (lengths, hq, hkv, d, causal, the launches' shapes)
 GROUP_CASES = [
-    # one row, one key: 3 of 4 groups see nothing
-    ([1], 1, 1, 64, True, [(8, 4, 1), (8, 4, 1), (8, 2, 1)]),
-    # a 64-row tile and one row
-    ([65], 3, 1, 128, True, [(8, 4, 1), (8, 4, 1), (8, 2, 6)]),
+    # one row, one key
+    ([1], 1, 1, 64, True, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
+    ([65], 3, 1, 128, True, [(4, 1, 1), (4, 1, 1), (8, 2, 6)]),
+    # from 256 keys on four groups; five 64-row tiles and one row
+    ([255], 3, 1, 128, True, [(4, 1, 1), (4, 1, 1), (8, 2, 12)]),
+    ([256], 3, 1, 128, True, [(8, 4, 1), (8, 4, 1), (8, 2, 12)]),
+    ([321], 3, 1, 64, True, [(8, 4, 1), (8, 4, 1), (8, 1, 9)]),
     # four groups, unsplit
     ([512], 8, 8, 64, True, [(8, 4, 1), (8, 4, 1), (8, 2, 3)]),
     ([511], 2, 2, 128, False, [(8, 4, 1), (4, 1, 4), (8, 2, 2)]),
     # two groups, balanced parts, one row in the last tile
-    ([2049], 1, 1, 128, True, [(8, 2, 9), (8, 2, 9), (8, 2, 11)]),
+    ([2049], 1, 1, 128, True, [(8, 1, 9), (8, 2, 9), (8, 2, 11)]),
+    ([2049], 2, 2, 128, True, [(8, 2, 9), (8, 2, 9), (8, 2, 11)]),
     # three query heads per key head
-    ([2500], 6, 2, 64, True, [(8, 2, 3), (8, 2, 3), (8, 2, 11)]),
-    # two groups, uniform parts
-    ([2304], 2, 1, 128, False, [(8, 2, 2), (8, 2, 2), (8, 1, 4)]),
+    ([2500], 6, 2, 64, True, [(8, 2, 3), (8, 2, 3), (8, 1, 15)]),
+    ([2500], 6, 2, 128, True, [(8, 2, 3), (8, 2, 3), (8, 2, 11)]),
+    # uniform parts: one group, and two
+    ([2304], 2, 1, 128, False, [(8, 1, 4), (8, 1, 4), (8, 1, 4)]),
+    ([2304], 4, 4, 128, False, [(8, 2, 2), (8, 2, 2), (8, 2, 2)]),
     # packed: dK/dV over 128-key tiles
     ([600, 1, 129, 1024] * 4, 3, 3, 128, True, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
     ([2048, 1000, 2000], 4, 2, 128, True, [(4, 1, 2), (4, 1, 2), (8, 2, 2)]),
     ([300, 1, 129, 512], 2, 1, 64, True, [(4, 1, 1), (4, 1, 1), (8, 1, 4)]),
     ([300, 0, 127], 4, 4, 128, False, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
     # d = 64: 300 8-wave tiles, so a 4-wave forward
-    ([2305], 30, 15, 64, True, [(4, 1, 1), (8, 2, 1), (8, 2, 2)]),
+    ([2305], 30, 15, 64, True, [(4, 1, 1), (8, 1, 2), (8, 2, 2)]),
     # the same, packed: 4-wave forward and dQ
     ([2100, 65], 30, 30, 64, True, [(4, 1, 1), (4, 1, 1), (8, 1, 1)]),
     # 4-wave query tiles in uniform parts
@@ -111,11 +117,11 @@ def test_last_partial_round(nseg, hq, hkv, d, causal):
 
 
 def test_last_partial_round_single():
-    """127 key and query tiles of 128 over two XCDs per head: the second round
+    """dQ and dK/dV over 127 tiles of 128 rows, two XCDs per head: the second round
     is four workgroups short."""
     from tests.test_gpu_parity import _sampled_parity
     w = wl.Workload("single16200_h4", [16200], 4, 4, 128)
-    assert _shapes([16200], 4, 4, 128, True) == [(8, 2, 1)] * 3
+    assert _shapes([16200], 4, 4, 128, True)[1:] == [(8, 2, 1)] * 2
     _sampled_parity(w, device_gen=True, heads=[0, 3], kv_heads=[1, 2], per_seg_random=48,
                     tail_cols=128)
 
@@ -187,10 +193,10 @@ def test_group_pairs(T, hq, hkv, d, causal, qs, ks, shapes):
 @pytest.mark.parametrize("T,hq,hkv,d,causal,chunk,shape", [
     (300, 4, 4, 128, True, None, (8, 4, 1)),
     (512, 8, 8, 64, True, None, (8, 4, 1)),
-    (2049, 1, 1, 128, True, None, (8, 2, 9)),     # two groups, balanced parts
+    (2049, 2, 2, 128, True, None, (8, 2, 9)),     # two groups, balanced parts
     (511, 2, 2, 128, False, None, (8, 4, 1)),
     (700, 1, 1, 64, False, None, (8, 4, 1)),
-    (2304, 2, 1, 128, False, None, (8, 2, 2)),    # two groups, uniform parts
+    (2304, 4, 2, 128, False, None, (8, 2, 2)),    # two groups, uniform parts
     (2600, 6, 6, 64, True, None, (4, 1, 4)),      # one group, parts
     (2100, 30, 30, 64, True, None, (4, 1, 1)),    # one group, no parts
     (2305, 1, 1, 128, True, (2305, 2305), (8, 2, 4)),

@@ -49,3 +49,40 @@ def test_packed_dkdv_groups(lengths, hq, hkv, d, causal, expect):
 def test_d64_four_wave_query_tiles(lengths, hq, fwd, dq):
     got = shapes(lengths, hq, hq, 64, True)
     assert (got["fwd_kernel"], got["bwd_dq_kernel"]) == (fwd, dq)
+
+
+@pytest.mark.parametrize("T,hq,hkv,d,causal,fwd,dq,dkdv", [
+    # split launches: half of the parts and two groups where that saves enough
+    (8192, 4, 4, 128, True, (8, 2, 2), (8, 2, 2), (8, 2, 2)),
+    (16128, 4, 4, 128, True, (8, 1, 4), (8, 2, 2), (8, 2, 2)),
+    (16384, 4, 4, 128, True, (8, 1, 2), (8, 2, 1), (8, 2, 1)),
+    (13433, 3, 3, 64, True, (8, 1, 4), (8, 1, 4), (8, 1, 4)),
+    (8192, 8, 8, 64, True, (8, 2, 1), (8, 2, 1), (8, 2, 1)),
+    (8853, 8, 8, 64, True, (8, 1, 2), (8, 1, 2), (8, 2, 1)),
+    (8192, 8, 8, 64, False, (8, 1, 2), (8, 1, 2), (8, 1, 2)),
+    # groups need 256 keys
+    (255, 4, 4, 64, True, (4, 1, 1), (4, 1, 1), (8, 2, 1)),
+    (256, 4, 4, 64, True, (8, 4, 1), (8, 4, 1), (8, 2, 1)),
+    # more than a round: not at d = 64 without a mask, nor (much more) for a
+    # causal forward
+    (24701, 8, 4, 64, False, (8, 1, 1), (8, 1, 1), (8, 1, 2)),
+    (2901, 32, 16, 128, True, (8, 1, 1), (8, 2, 1), (8, 2, 2)),
+    # 4-wave query tiles at d = 64: dQ with few heads up to two rounds
+    (38243, 4, 4, 64, True, (4, 1, 1), (8, 1, 1), (8, 1, 1)),
+    (17045, 8, 8, 64, True, (4, 1, 1), (4, 1, 1), (8, 1, 1)),
+])
+def test_single_sequences(T, hq, hkv, d, causal, fwd, dq, dkdv):
+    got = shapes([T], hq, hkv, d, causal)
+    assert (got["fwd_kernel"], got["bwd_dq_kernel"], got["bwd_dkdv_kernel"]) == (fwd, dq, dkdv)
+
+
+@pytest.mark.parametrize("tq,tk,qo,d,fwd", [
+    (16384, 16384, 0, 64, (8, 2, 1)),       # over the diagonal, 256 workgroups
+    (16896, 16896, 67584, 64, (8, 1, 1)),   # all keys visible, more than a round
+    (8192, 8192, 8192, 64, (8, 2, 1)),
+    (1024, 1024, 1024, 64, (8, 4, 1)),      # too few keys for parts
+    (1024, 1280, 4096, 64, (8, 2, 2)),
+    (1024, 255, 4096, 64, (4, 1, 1)),
+])
+def test_pairs(tq, tk, qo, d, fwd):
+    assert P.chunk_launch_shapes(tq, tk, qo, 0, 4, 4, d)["fwd_kernel"] == fwd
