@@ -249,13 +249,14 @@ constexpr int kMaxParts = 16;  // partial slices of a balanced split at most
 pdy::Split balanced_split(pdy::Split shape, int p, int64_t heads, double unit_us,
                           double slice_bytes) {
   if ((int64_t)p * shape.nitems * heads > kCUs) return uniform_split(p);
-  const int umax = shape.units(0);  // item 0 is the heaviest
+  int units[kCUs];  // (nitems <= kCUs by the line above)
   int64_t total_units = 0;
-  for (int i = 0; i < shape.nitems; ++i) total_units += shape.units(i);
+  for (int i = 0; i < shape.nitems; ++i) total_units += units[i] = shape.units(i);
+  const int umax = units[0];  // item 0 is the heaviest
   const double mean_load = (double)total_units * heads / kCUs;
   auto entries = [&](int cap) {
     int64_t n = 0;
-    for (int i = 0; i < shape.nitems; ++i) n += (shape.units(i) + cap - 1) / cap;
+    for (int i = 0; i < shape.nitems; ++i) n += (units[i] + cap - 1) / cap;
     return n * heads;
   };
   auto cap_for = [&](int64_t budget) {
@@ -403,14 +404,19 @@ double est_unsplit_us(Which k, const Job& j, const Shape& sh) {
   const bool kv = k == DKDV;
   const Sizes &mine = kv ? j.sk : j.sq, &other = kv ? j.sq : j.sk;
   const int64_t heads = kv ? j.sk.hkv : j.sq.hq, g = kv ? j.sq.hq / j.sq.hkv : 1;
-  const int64_t step = kv ? 64 : 128, n = tiles_of(mine, tile);
+  const int step_log2 = kv ? 6 : 7;
+  const int64_t round_up = (1 << step_log2) - 1, n = tiles_of(mine, tile);
   int64_t total = 0, most = 0, least = INT64_MAX;
-  for (int64_t i = 0; i < n; ++i) {
-    int64_t seen = other.T;  // rows or keys that the tile visits
-    if (j.causal)
-      seen = kv ? other.T - std::min(other.T, std::max<int64_t>(0, i * tile - j.shift))
-                : std::max<int64_t>(0, std::min(other.T, (i + 1) * tile + j.shift));
-    const int64_t u = (seen + step - 1) / step * g;
+  if (!j.causal) {
+    most = least = ((other.T + round_up) >> step_log2) * g;
+    total = n * most;
+  }
+  for (int64_t i = 0; j.causal && i < n; ++i) {
+    // rows or keys that the tile visits
+    const int64_t seen =
+        kv ? other.T - std::min(other.T, std::max<int64_t>(0, i * tile - j.shift))
+           : std::max<int64_t>(0, std::min(other.T, (i + 1) * tile + j.shift));
+    const int64_t u = ((seen + round_up) >> step_log2) * g;
     total += u;
     most = std::max(most, u);
     least = std::min(least, u);
@@ -429,8 +435,8 @@ constexpr int64_t kAverageShort = 512;
 // launches of this many workgroups fill the chip in any shape
 constexpr int64_t kManyItems = 1024;
 
-Launch pick(Which k, const Job& j) {
-  const Launch base = base_launch(k, j);
+// The launch for a job; `base`: that of base_launch, which a small workspace gets.
+Launch pick(Which k, const Job& j, const Launch& base) {
   const Work w = work_of(k, j, base.sh);
   const int64_t n = w.items * w.heads;
   auto shape = [&](int groups) { return Shape{8, groups}; };
@@ -615,7 +621,8 @@ size_t fwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
   size_t n = 0;
   for (int causal = 0; causal <= 1; ++causal) {
     const Job j{sq, sk, causal, chunk, 0};
-    n = std::max({n, fwd_need(pick(FWD, j), sq), fwd_need(base_launch(FWD, j), sq)});
+    const Launch base = base_launch(FWD, j);
+    n = std::max({n, fwd_need(pick(FWD, j, base), sq), fwd_need(base, sq)});
   }
   return n;
 }
@@ -623,8 +630,9 @@ size_t bwd_workspace_bytes(const Sizes& sq, const Sizes& sk, bool chunk) {
   size_t n = 0;
   for (int causal = 0; causal <= 1; ++causal) {
     const Job j{sq, sk, causal, chunk, 0};
-    n = std::max({n, bwd_need(pick(DKDV, j), pick(DQ, j), sq, sk),
-                  bwd_need(base_launch(DKDV, j), base_launch(DQ, j), sq, sk)});
+    const Launch kv = base_launch(DKDV, j), q = base_launch(DQ, j);
+    n = std::max({n, bwd_need(pick(DKDV, j, kv), pick(DQ, j, q), sq, sk),
+                  bwd_need(kv, q, sq, sk)});
   }
   return n;
 }
@@ -824,11 +832,12 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
                     const char* who) {
   pdy_status st;
   const Job job{s, sk, causal, c.on != 0, c.shift};
-  Launch l = pick(FWD, job);
+  const Launch base = base_launch(FWD, job);
+  Launch l = pick(FWD, job, base);
   // (a pair whose workspace was sized for other chunks takes fewer parts)
   while (c.on && workspace_bytes < fwd_need(l, s) && l.split.parts > 1)
     l.split = halve_split(l.split);
-  if (workspace_bytes < fwd_need(l, s)) l = base_launch(FWD, job);
+  if (workspace_bytes < fwd_need(l, s)) l = base;
   const size_t need = fwd_need(l, s);
   if (workspace_bytes < need)
     return fail(PDY_ERR_WORKSPACE, "workspace has %zu bytes, %s needs %zu", workspace_bytes, who,
@@ -894,7 +903,8 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
                     const char* who, bool fit_splits) {
   pdy_status st;
   const Job job{s, sk, causal, c.on != 0, c.shift};
-  Launch lk = pick(DKDV, job), lq = pick(DQ, job);
+  const Launch base_k = base_launch(DKDV, job), base_q = base_launch(DQ, job);
+  Launch lk = pick(DKDV, job, base_k), lq = pick(DQ, job, base_q);
   // fit_splits: a workspace of fixed size, or sized for other chunks, takes
   // fewer split-K parts (the larger partial buffer halved first) when the chosen
   // ones do not fit
@@ -909,8 +919,8 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     return bwd_need(lk, lq, s, sk) <= workspace_bytes;
   };
   if (!fits()) {
-    lk = base_launch(DKDV, job);
-    lq = base_launch(DQ, job);
+    lk = base_k;
+    lq = base_q;
     if (!fits())
       return fail(PDY_ERR_WORKSPACE, "workspace has %zu bytes, %s needs %zu", workspace_bytes, who,
                   bwd_need(lk, lq, s, sk));
@@ -1089,7 +1099,7 @@ void write_shapes(const Job& j, int32_t* out) {
   const bool runs[3] = {j.sq.T > 0, j.sq.T > 0, j.sq.T > 0 && j.sk.T > 0};
   for (int k = 0; k < 3; ++k) {
     if (!runs[k]) continue;
-    const Launch l = pick((Which)k, j);
+    const Launch l = pick((Which)k, j, base_launch((Which)k, j));
     out[3 * k] = l.sh.nw;
     out[3 * k + 1] = l.sh.groups;
     out[3 * k + 2] = l.split.parts;
