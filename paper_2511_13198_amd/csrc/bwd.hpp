@@ -763,7 +763,9 @@ __global__ void __launch_bounds__(NW * 64, D == 64 && NW == 8 && KG == 1 ? 4 : N
   store_rows_f32<D, C::F32_PASS>(
       dqa, a.scale, split ? a.part_dq + (size_t)part * a.total_tokens * qstride + off : a.dq + off,
       qstride, seg_hi - wrow0, a.accumulate && !split,
-      reinterpret_cast<float*>(smem) + w * C::F32_PASS * kF32Block);
+      reinterpret_cast<float*>(smem) + w * C::F32_PASS * kF32Block,
+      // (d = 64, 8 waves: two registers short of its 128 otherwise)
+      D == 64 && NW == 8 ? fresh_lane_id() : l);
 }
 
 }  // namespace pdy

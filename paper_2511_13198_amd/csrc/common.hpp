@@ -352,6 +352,13 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
   asm volatile("" ::: "memory");
 }
+// The lane index, computed anew: what an epilogue derives from it then holds no
+// registers over the tile loop.
+__device__ __forceinline__ int fresh_lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 // Four 16-byte LDS reads at byte offsets O0..O3 from addr, waited for.
 template <int O0, int O1, int O2, int O3>
 __device__ __forceinline__ void lds_read4(uint32_t addr, u32x4 (&v)[4]) {
@@ -372,8 +379,7 @@ __device__ __forceinline__ void lds_read4(uint32_t addr, u32x4 (&v)[4]) {
 // conflict-free written by rows of accumulators and read by rows of columns).
 constexpr int kF32Pitch = 36;
 constexpr int kF32Block = 32 * kF32Pitch;
-__device__ __forceinline__ int acc_slot_lane() {
-  const int l = __lane_id();
+__device__ __forceinline__ int acc_slot_lane(int l = __lane_id()) {
   return (l & 31) * kF32Pitch + (l >> 5) * 4;
 }
 __device__ __forceinline__ void acc_to_lds(const f32x16& x, float mul, float* block, int lane_off) {
@@ -386,15 +392,14 @@ __device__ __forceinline__ void acc_to_lds(const f32x16& x, float mul, float* bl
 // One wave's 32 rows of D floats, acc * mul (mul: this lane's row's factor), to
 // dst (row 0, column 0; `stride` floats from row to row), rows < nrows only;
 // accumulate: added to what dst holds.  PASS blocks are turned at a time:
-// PASS * kF32Block floats of LDS per wave.
+// PASS * kF32Block floats of LDS per wave.  l: the lane index.
 template <int D, int PASS>
 __device__ __forceinline__ void store_rows_f32(const f32x16 (&acc)[D / 32], float mul, float* dst,
                                                size_t stride, int nrows, bool accumulate,
-                                               float* lds) {
+                                               float* lds, int l = __lane_id()) {
   static_assert((D / 32) % PASS == 0, "whole passes");
   if (nrows <= 0) return;  // wave-uniform
-  const int l = __lane_id();
-  const int wr = acc_slot_lane();
+  const int wr = acc_slot_lane(l);
   const int rr = l >> 3, c = (l & 7) * 4;  // read: 8 lanes a row
   const uint32_t rd = lds_addr(lds) + (rr * kF32Pitch + c) * 4;
   // (one address per lane, then uniform steps of 8 rows)

@@ -100,6 +100,13 @@ def test_no_use_of_lds_read_destinations_before_their_wait():
         f"  {k}: {a}  ...  {b}" for k, a, b in hazards[:20])
 
 
+def test_no_kernel_uses_scratch_memory():
+    """No kernel keeps registers in memory (the runtime would have to allocate
+    it for the launch, and the reload stands before a workgroup's stores)."""
+    sizes = re.findall(r"^\s*\.private_segment_fixed_size:\s*(\d+)", device_asm(), re.M)
+    assert len(sizes) > 20 and not any(int(x) for x in sizes)
+
+
 def test_checker_flags_a_planted_early_use():
     """The walk itself: a copy of an in-flight destination is reported, the
     same copy after a covering wait is not, and a wait that leaves the read
