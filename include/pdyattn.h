@@ -41,15 +41,22 @@
  *   - Launches too small to fill the GPU (fewer than 512 work items, e.g. a
  *     single 8K-token sequence over 4 heads) split each item's work into
  *     parts (split-K) whose fp32 partial results are combined in a second
- *     kernel: 2 or 4 parts per item, or, for a causal single sequence whose
- *     parts fit one round on the GPU, more parts for the heavier items (at
- *     most 16), or among the waves of a workgroup; the choice depends only on
- *     the sizes, the causal flag (the workspace queries cover both values of
- *     the flag) and, for a chunk pair, its offsets.  A chunk pair in a workspace
- *     too small for its parts takes fewer.  A segment's results
- *     therefore do not depend on the other segments of its batch, but a batch
- *     and the same segment alone may round differently when one of the two
- *     launches is split.
+ *     kernel (2 or 4 parts per item, or, for a causal single sequence whose
+ *     parts fit one round on the GPU, at most 16, more for the heavier items),
+ *     or among groups of a workgroup's waves; and short or few segments take
+ *     smaller workgroups.  This shape of a launch (pdy_launch_shapes) follows
+ *     from its sizes -- total_tokens, num_seqs, max_seqlen and the head counts
+ *     and dimension, so from the whole batch -- the causal flag (the workspace
+ *     queries cover both values), a chunk pair's offsets, and the workspace: one
+ *     smaller than the query asks for is taken where it holds fewer parts (chunk
+ *     pairs) or the shape without groups, and refused else.
+ *   - Results depend on the shape in rounding only (which keys share an exponent
+ *     offset, the order of fp32 sums; the error against exact arithmetic is the
+ *     same).  A segment's results do not depend on the contents of the other
+ *     segments of its batch, but they are bitwise those of the same segment
+ *     alone, or in another batch, only where the launches have one shape without
+ *     parts.
+ *   - A row that sees a NaN or +inf logit gets o = NaN and lse = -inf.
  */
 #ifndef PDYATTN_H
 #define PDYATTN_H
@@ -178,9 +185,9 @@ pdy_status attn_validate_cu_seqlens(const int32_t* cu_seqlens, int32_t num_seqs,
  * D alone exceed 64 MiB (Hq * T beyond about 16.7 million (row, head)
  * pairs) return PDY_ERR_WORKSPACE before anything is launched.  A launch
  * small enough to split (see above) whose partial gradients would not fit
- * takes fewer parts; its results may then differ from attn_bwd's in
- * rounding (well inside the stated tolerance), otherwise they equal
- * attn_bwd's bit for bit.  The call allocates nothing (no hipMalloc, no
+ * takes fewer parts, and one whose tile schedule would not fit another shape;
+ * its results may then differ from attn_bwd's in rounding (well inside the
+ * stated tolerance), otherwise they equal attn_bwd's bit for bit.  The call allocates nothing (no hipMalloc, no
  * library allocation); on its first use on a device it looks up that
  * device's address of the array.  The array keeps the last call's contents,
  * none of which a call reads before writing it.  Every call on one GPU uses

@@ -131,20 +131,10 @@ def test_forward_logits_rising_past_first_keys(lengths, hq, hkv, d, causal):
     pu.check_close("LSE", lse.cpu().numpy(), rlse)
 
 
-def _run_counted(dev, cu_d, max_seqlen, scale):
-    """run_gpu, and whether any split-K combining kernel ran."""
-    from paper_2511_13198_amd import pdyattn
-    pdyattn.profile_start()
-    out = pu.run_gpu(dev["q"], dev["k"], dev["v"], dev["do"], cu_d, max_seqlen, True, scale)
-    prof = pdyattn.profile_stop()
-    return out, any(k in prof for k in ("split_merge_kernel", "split_sum_kernel"))
-
-
 def _same(a, b, exact, what):
-    """Bitwise when both launches took the same path.  Otherwise (one of them
-    split-K) within the parity tolerance: the forward's O may round to the
-    neighbouring bf16 value, which moves D = rowsum(dO * O) and with it the
-    gradients by about 1e-3 relative."""
+    """Bitwise when both launches have one shape.  Otherwise within the parity
+    tolerance: the forward's O may round to the neighbouring bf16 value, which
+    moves D = rowsum(dO * O) and with it the gradients by about 1e-3 relative."""
     import torch
     if exact:
         assert torch.equal(a, b), f"{what} differs"
@@ -154,20 +144,26 @@ def _same(a, b, exact, what):
 
 @pytest.mark.parametrize("lengths,hq,hkv", [
     ([300, 129, 511], 4, 2),       # small: the lone segments run split-K
+    ([300, 256, 299], 16, 16),     # nothing split: four key groups alone, one packed
     ([4096, 6000, 4500], 64, 32),  # every launch fills the chip: bitwise throughout
 ])
 def test_determinism_and_isolation(lengths, hq, hkv):
     """A second run gives the same bytes; a packed batch gives each segment
-    what it gets alone (bitwise unless one of the two launches is split-K);
+    what it gets alone (bitwise where both are one launch shape without parts);
     future keys do not change earlier rows (bitwise, same launch)."""
     import torch
+    from paper_2511_13198_amd import pdyattn
     d = 128
     T = sum(lengths)
     dev = wl.device_inputs(T, hq, hkv, d, seed=3)
     cu = wl.cu_from_lengths(lengths)
     cu_d = torch.from_numpy(cu).cuda()
-    r1, split1 = _run_counted(dev, cu_d, max(lengths), 0.09)
-    r2, _ = _run_counted(dev, cu_d, max(lengths), 0.09)
+
+    def run(x, offsets, maxlen):
+        return pu.run_gpu(x["q"], x["k"], x["v"], x["do"], offsets, maxlen, True, 0.09)
+
+    r1, r2 = run(dev, cu_d, max(lengths)), run(dev, cu_d, max(lengths))
+    packed = pdyattn.launch_shapes(T, len(lengths), max(lengths), hq, hkv, d)
     for a, b in zip(r1, r2):
         assert torch.equal(a, b), "non-deterministic output"
     names = ("O", "LSE", "dQ", "dK", "dV")
@@ -175,10 +171,12 @@ def test_determinism_and_isolation(lengths, hq, hkv):
         a, b = int(cu[si]), int(cu[si + 1])
         cu1 = torch.tensor([0, b - a], dtype=torch.int32, device="cuda")
         seg = {n: dev[n][a:b].contiguous() for n in ("q", "k", "v", "do")}
-        alone, split_a = _run_counted(seg, cu1, b - a, 0.09)
-        exact = not (split1 or split_a)
-        if len(lengths) == 3 and lengths[0] == 4096:
-            assert exact, "the large case is meant to run without split-K"
+        alone = run(seg, cu1, b - a)
+        shapes = pdyattn.launch_shapes(b - a, 1, b - a, hq, hkv, d)
+        parts = any(s[2] > 1 for s in (*packed.values(), *shapes.values()))
+        exact = shapes == packed and not parts
+        # what each case is there for
+        assert parts == (hq == 4) and exact == (hq == 64), (packed, shapes)
         _same(alone[0], r1[0][a:b], exact, f"segment {si}: O")
         _same(alone[1], r1[1][:, a:b], exact, f"segment {si}: LSE")
         for t in (2, 3, 4):
@@ -190,7 +188,7 @@ def test_determinism_and_isolation(lengths, hq, hkv):
     q2[i + 1:] = 3.0
     k2[i + 1:] = -2.0
     v2[i + 1:] = 7.0
-    r3, _ = _run_counted({"q": q2, "k": k2, "v": v2, "do": dev["do"]}, cu_d, max(lengths), 0.09)
+    r3 = run({"q": q2, "k": k2, "v": v2, "do": dev["do"]}, cu_d, max(lengths))
     assert torch.equal(r3[0][: i + 1], r1[0][: i + 1])
     assert torch.equal(r3[1][:, : i + 1], r1[1][:, : i + 1])
     assert torch.equal(r3[2][: i + 1], r1[2][: i + 1])
