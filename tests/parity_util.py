@@ -34,6 +34,38 @@ def check_close(name: str, got, ref, max_abs: float = MAX_ABS, rel_l2: float = R
     return mx, rel
 
 
+# largest relative L2 error of a block of 64 rows of one head: measured up to
+# 3e-3 (a whole tensor: 2e-3) and 4.8e-3 in segments of fewer rows; twice that
+BLOCK_REL_L2 = 1e-2
+
+
+def check_blocks(name: str, got, ref, cu, rel_l2: float = BLOCK_REL_L2, rows: int = 64):
+    """Every block of `rows` rows of every segment and head of [T, H, d] tensors
+    against its own reference norm: under a causal mask a sequence's first keys
+    hold nearly all of dK's and dV's energy, so that a lost late tile passes any
+    bound on the whole tensor.  A segment's last block takes its remainder;
+    segments of fewer than 16 rows (few, largely cancelling terms) are left to
+    the bound on the whole."""
+    got = np.asarray(got, dtype=np.float64)
+    ref = np.asarray(ref, dtype=np.float64)
+    worst, where = 0.0, None
+    for a, b in zip(cu[:-1], cu[1:]):
+        a, b = int(a), int(b)
+        if b - a < 16:
+            continue
+        starts = a + rows * np.arange(max(1, (b - a) // rows))
+        err = np.add.reduceat(np.sum((got[a:b] - ref[a:b]) ** 2, axis=2), starts - a, axis=0)
+        nrm = np.add.reduceat(np.sum(ref[a:b] ** 2, axis=2), starts - a, axis=0)
+        rel = np.sqrt(err / np.maximum(nrm, 1e-300))
+        i = np.unravel_index(np.argmax(rel), rel.shape)
+        if rel[i] > worst:
+            worst, where = float(rel[i]), (int(starts[i[0]]), int(i[1]))
+    log(f"    {name:5s} worst block relL2 {worst:.3e} (row {where and where[0]}, "
+        f"head {where and where[1]})")
+    assert worst <= rel_l2, f"{name}: rows from {where[0]} of head {where[1]}: {worst:.3e} > {rel_l2}"
+    return worst
+
+
 class HeadView:
     """[T, H, d] bf16 tensor (host or device) handed to the oracle one head at
     a time, widened exactly to float64 on the host."""

@@ -39,6 +39,8 @@ def _full_parity(lengths, hq, hkv, d, causal, scale=None, seed=wl.SEED):
     pu.check_close("dQ", dq.cpu().numpy(), rdq)
     pu.check_close("dK", dk.cpu().numpy(), rdk)
     pu.check_close("dV", dv.cpu().numpy(), rdv)
+    for name, got, ref in (("O", o, ro), ("dQ", dq, rdq), ("dK", dk, rdk), ("dV", dv, rdv)):
+        pu.check_blocks(name, got.double().cpu().numpy(), ref, cu)
     return (o, lse, dq, dk, dv), dev, cu_d
 
 
