@@ -4,16 +4,18 @@
 //   dV = P^T dO,  dP = dO V^T,  dS = P * (dP - D),  dK = scale * dS^T Q,
 //   dQ = scale * dS K.
 // Two kernels, in this order:
-//   * bwd_dq_kernel     one workgroup per (segment, query head, 32-row-per-wave
-//                       tile); mirrors the forward: computes its rows'
-//                       D = rowsum(dO * O) (fp32, written to [Hq, T] for the
-//                       next kernel), recomputes S^T and dP^T, forms dS^T and
-//                       accumulates dQ^T = K^T dS^T.  No atomics.
-//   * bwd_dkdv_kernel   one workgroup per (segment, kv head, 256-key tile); a
-//                       wave owns 32 keys (K in an LDS tile, V in registers),
-//                       keeps their dK^T / dV^T in accumulators, and sweeps
-//                       every query head of the group and every 64-row query
-//                       step that sees the keys.  Written once, no atomics.
+//   * bwd_dq_kernel     one workgroup per (segment, query head, query tile), with
+//                       key groups or not, as in the forward, which it mirrors:
+//                       computes its rows' D = rowsum(dO * O) (fp32, written to
+//                       [Hq, T] for the next kernel), recomputes S^T and dP^T,
+//                       forms dS^T and accumulates dQ^T = K^T dS^T.  No atomics.
+//   * bwd_dkdv_kernel   one workgroup per (segment, kv head, key tile): 8 waves
+//                       over 256 keys, 8 in two query groups over 128, or 4 over
+//                       128.  A wave has 32 keys (K in an LDS tile, V in
+//                       registers), keeps their dK^T / dV^T in accumulators, and
+//                       sweeps every query head of the group and every query step
+//                       of 64 rows (4 waves at d = 128: 32; a query group half of
+//                       each) that sees the keys.  Written once, no atomics.
 // When a launch cannot fill the chip, a workgroup takes one part of a tile's
 // work (split-K) and one split_sum_kernel launch adds the parts' partial
 // gradients of both.
@@ -345,8 +347,8 @@ __global__ void __launch_bounds__(NWAVES * 64, NWAVES == 4 ? 2 : D == 64 ? 3 : 1
     // the two waves of a SIMD run the same phases at about the same time;
     // raising the priority of a wave in this product-only phase lets it keep
     // the matrix core fed while the other wave's exponentials fill the
-    // vector ALU (measured: dK/dV 2% faster; no gain in the other phase or
-    // the other kernels)
+    // vector ALU (dK/dV 2 % faster; no gain in the other phase).  dQ and, for
+    // one of the two waves, the forward do the same.
     __builtin_amdgcn_s_setprio(1);
     static_for<NDB>([&](auto DB) { tr_issue<QL, 0, DB * 32>(ga, ra[DB]); });
     static_for<NDB>([&](auto DB) { tr_issue<QL, 0, DB * 32>(qa, rb[DB]); });

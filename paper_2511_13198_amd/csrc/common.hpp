@@ -668,7 +668,8 @@ __device__ __forceinline__ bool split_entry_scan(const Split& sp, int entry, int
 // order (a ballot per level and 64 segments).  Against plan_kernel (5-6 us and a
 // launch per call): forward + backward of 33 segments of 184 tokens x 8 heads of
 // 64 49.2 -> 40.0 us, 70 of 16-107 x 16 59.3 -> 51.7, 32 of 512 x 16 272 -> 257;
-// 122 of 16-512 tokens x 32/8 heads unchanged (the kernels take 2 % longer).
+// 122 of 16-512 tokens x 32/8 heads unchanged (the kernels take 2 % longer).  (The
+// segment-major order's pass also bounds segments x workgroups.)
 constexpr int kDirectSegMajor = 64;
 constexpr int kDirectChunks = 2;
 

@@ -1,21 +1,22 @@
 // Forward of Eq. (2) (section 3): tiled online-softmax attention on the bf16
 // matrix cores of gfx950.
 //
-// One workgroup = one (segment, query head, query tile of 32*NW rows).  With
-// NW = 8 two waves share each SIMD, so one wave's softmax (VALU) overlaps the
-// other's matrix products.  Each wave owns 32 query rows, with Q held in
-// registers as the B operand of
+// One workgroup = one (segment, query head, query tile): NW waves over 32*NW
+// rows, or KG key groups of them over 32*NW/KG rows, each group with its share of
+// every key tile.  With NW = 8 two waves share each SIMD, so one wave's softmax
+// (VALU) overlaps the other's matrix products.  A wave has 32 query rows, with Q
+// held in registers as the B operand of
 //   S^T = K Q^T            (32 keys x 32 rows per MFMA tile, keys from LDS)
 // so that each lane owns one query row (l % 32) and half of the keys of a
 // tile; the row max / row sum need one cross-half exchange (permlane32_swap).
 // The probabilities are rounded to bf16 and fed back as the B operand of
 //   O^T += V^T P^T          (32 head-dim x 32 rows per MFMA tile)
 // with V^T read from the row-major LDS tile by transposing reads.  K/V tiles
-// (128 keys at d = 128 with 8 waves, else 64) reach LDS by direct copies;
-// tile t+1 is in flight while tile t is computed, in softmax steps of 64
-// keys.  Tiles entirely above the causal
-// diagonal are never visited; only tiles crossing the diagonal or the segment
-// end are masked.  When a launch has too few query tiles to fill the chip, a
+// (128 keys at d = 128 with 8 waves and with key groups, else 64) reach LDS by
+// direct copies; tile t+1 (with key groups at d = 64 also t+2 and t+3) is in
+// flight while tile t is computed, in softmax steps of 64 keys (32 with four
+// groups).  Tiles entirely above the causal diagonal are never visited; only
+// tiles crossing the diagonal or the segment end are masked.  When a launch has too few query tiles to fill the chip, a
 // workgroup takes one contiguous part of its query tile's key tiles (split-K)
 // and writes a partial O and LSE that split_merge_kernel combines.
 //
@@ -273,9 +274,9 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
            (!a.causal || k0 <= wrow_last + shift);
   };
 
-  // S^T for the tile's 32-key blocks; the independent chains interleave
-  // S^T for the tile's two 32-key blocks; K fragments are read PIPE k-steps
-  // ahead of the products that consume them
+  // S^T for a softmax step's one or two 32-key blocks (independent chains that
+  // interleave); K fragments are read PIPE k-steps ahead of the products that
+  // consume them
   auto compute_s = [&](const uint16_t* ktile, auto&& hook) __attribute__((always_inline)) {
     constexpr int NKS = D / 16, NKB = BKS / 32;
     static_assert(NKB == 1 || NKB == 2, "one or two 32-key blocks per step");
@@ -361,10 +362,13 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) fwd_kernel(FwdArgs a
     // phases (in the S^T products it is 1.6 % slower) -- at d = 128 with 8 waves,
     // whose wave w shares a SIMD with wave w + 4 alone, only for the second of the
     // two: it runs ahead of the first by about a phase, so one's exponentials meet
-    // the other's products more often than when both raise theirs (638,976 tokens
-    // x 1 head 0.5-0.7 % faster on three cards, e.g. 87.76 -> 87.16 ms; whole steps
-    // change within their noise; the backward's kernels lose 1-2 % that way, and
-    // d = 64, with four waves per SIMD, 3-9 %)
+    // the other's products more often than when both raise theirs.  Against that,
+    // in turn on two cards: 638,976 tokens x 1 head 88.90 -> 88.47 and 88.33 ->
+    // 87.52 ms, 131,072 x 4 15.05 -> 14.93 and 14.99 -> 14.75, 65,536 in 25
+    // segments x 32 2.397 -> 2.351 and 2.426 -> 2.369, the long-tailed 262,144 x
+    // 32/8 22.38 -> 21.97 and 22.57 -> 22.25.  It costs 12 registers (187 -> 199)
+    // and three scalars kept in a vector register over the loop.  (The backward's
+    // kernels lose 1-2 % that way, and d = 64, with four waves per SIMD, 3-9 %.)
     if (D == 64 || NW == 4 || w >= 4) __builtin_amdgcn_s_setprio(1);
     static_for<NDB>([&](auto DB) { tr_issue<VL, 0, DB * 32>(va, vr[0][DB]); });
     static_for<NT16>([&](auto T) {

@@ -32,13 +32,15 @@ pdy_status hip_fail(hipError_t e, const char* what) {
   return fail(PDY_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-constexpr int kTile = 128;  // smallest tile of any kernel (bounds the work items)
+// Smallest tile of a launch that can be large, which bounds the work items (the
+// 64-row tiles of four key groups are only for launches of under kManyItems
+// workgroups of larger ones).
+constexpr int kTile = 128;
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 struct Sizes {
   int64_t T, N, maxlen, hq, hkv, d;
-  int max_nt;  // tiles of kTile in the longest segment (unused by the launches)
 };
 
 int tiles_of(const Sizes& s, int tile) {
@@ -98,8 +100,6 @@ pdy_status check_sizes(int32_t T, int32_t N, int32_t maxlen, int32_t hq, int32_t
   out->hq = hq;
   out->hkv = hkv;
   out->d = d;
-  out->max_nt = (int)((maxlen + kTile - 1) / kTile);
-  if (out->max_nt < 1) out->max_nt = 1;
   return PDY_OK;
 }
 
