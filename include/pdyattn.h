@@ -47,7 +47,8 @@
  *     smaller workgroups.  This shape of a launch (pdy_launch_shapes) follows
  *     from its sizes -- total_tokens, num_seqs, max_seqlen and the head counts
  *     and dimension, so from the whole batch -- the causal flag (the workspace
- *     queries cover both values), a chunk pair's offsets, and the workspace: one
+ *     queries cover both values), a chunk pair's offsets and how many run at a
+ *     time, and the workspace: one
  *     smaller than the query asks for is taken where it holds fewer parts (chunk
  *     pairs) or the shape without groups, and refused else.
  *   - Results depend on the shape in rounding only (which keys share an exponent
@@ -161,6 +162,26 @@ pdy_status attn_bwd_chunk(const void* q, const void* k, const void* v, const voi
                           float* dq, float* dk, float* dv, int32_t accumulate,
                           void* workspace, size_t workspace_bytes, void* stream);
 
+/* The same two calls for a caller that runs `launches` (>= 1) such pairs of about
+ * these sizes at a time, on as many streams: the launch's shape then leaves the
+ * chip to them together.  attn_fwd_chunk and attn_bwd_chunk are launches = 1.
+ * (Each call has its own outputs and workspace, as any concurrent calls.) */
+pdy_status attn_fwd_chunk_shared(const void* q, const void* k, const void* v, int32_t tq,
+                                 int32_t tk, int32_t q_offset, int32_t k_offset,
+                                 int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                                 int32_t causal, float scale,
+                                 void* o, float* lse,
+                                 void* workspace, size_t workspace_bytes, void* stream,
+                                 int32_t launches);
+pdy_status attn_bwd_chunk_shared(const void* q, const void* k, const void* v, const void* o,
+                                 const float* lse, const void* dout, int32_t tq, int32_t tk,
+                                 int32_t q_offset, int32_t k_offset,
+                                 int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                                 int32_t causal, float scale,
+                                 float* dq, float* dk, float* dv, int32_t accumulate,
+                                 void* workspace, size_t workspace_bytes, void* stream,
+                                 int32_t launches);
+
 /* Combine two partial results of the same T query rows:
  *   lse = log(exp(lse_a) + exp(lse_b)),  o = sum_x exp(lse_x - lse) o_x
  * (bf16 [T, Hq, d] and fp32 [Hq, T]).  o/lse may alias o_a/lse_a or
@@ -210,7 +231,7 @@ pdy_status pdy_launch_shapes(int32_t total_tokens, int32_t num_seqs, int32_t max
                              int32_t causal, int32_t* shapes);
 pdy_status pdy_chunk_launch_shapes(int32_t tq, int32_t tk, int32_t q_offset, int32_t k_offset,
                                    int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
-                                   int32_t causal, int32_t* shapes);
+                                   int32_t causal, int32_t launches, int32_t* shapes);
 
 /* Static text for a status code. */
 const char* pdy_status_string(int32_t status);

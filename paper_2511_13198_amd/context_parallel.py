@@ -210,6 +210,7 @@ def ring_forward(q, k, v, p: int, causal: bool = True, scale: Optional[float] = 
                               torch.empty((hq, n), dtype=torch.float32, device=q.device)))
         # longest chains first, each on the less loaded stream
         load = [0, 0]
+        at_a_time = min(2, len(chains))
         order = sorted(range(len(chains)),
                        key=lambda c: -sum(pair_count(chains[c][0], kr, causal)
                                           for kr in chains[c][1]))
@@ -224,10 +225,10 @@ def ring_forward(q, k, v, p: int, causal: bool = True, scale: Optional[float] = 
                 for j, (ka, kb) in enumerate(krs):
                     if j == 0:
                         pdyattn.attn_fwd_chunk(q[qa:qb], k[ka:kb], v[ka:kb], qa, ka, causal,
-                                               scale, out=po, lse=pl)
+                                               scale, out=po, lse=pl, launches=at_a_time)
                     else:
                         part = pdyattn.attn_fwd_chunk(q[qa:qb], k[ka:kb], v[ka:kb], qa, ka,
-                                                      causal, scale)
+                                                      causal, scale, launches=at_a_time)
                         pdyattn.attn_merge(po, pl, part[0], part[1], out=po, lse=pl)
         for st in side:
             main.wait_stream(st)
@@ -275,7 +276,7 @@ def ring_backward(q, k, v, o, lses: Dict[Range, object], dout, p: int, causal: b
                         pdyattn.attn_bwd_chunk(q[qa:qb], k[ka:kb], v[ka:kb], o[qa:qb],
                                                lses[(qa, qb)], dout[qa:qb], qa, ka, causal, scale,
                                                dq=dq[qa:qb], dk=dk[ka:kb], dv=dv[ka:kb],
-                                               accumulate=accumulate)
+                                               accumulate=accumulate, launches=len(group))
                 for i in range(len(group)):
                     main.wait_stream(side[i])
     return dq, dk, dv

@@ -307,13 +307,14 @@ struct Launch {
 };
 
 // What the choice of a launch looks at: rows of queries over rows of keys, sq
-// and sk (one chunk each, `shift` apart, for a context-parallel pair; the same
-// segments otherwise).
+// and sk (one chunk each, `shift` apart, for a context-parallel pair, of which
+// `launches` run at a time; the same segments otherwise).
 struct Job {
   const Sizes &sq, &sk;
   int causal;
   bool chunk;
   int shift;
+  int launches = 1;  // chunk pairs at a time
 };
 
 enum Which { FWD, DQ, DKDV };
@@ -530,15 +531,15 @@ Launch pick(Which k, const Job& j, const Launch& base) {
   }
   // a 4-wave launch that has a workgroup for every CU is left alone
   if (j.sk.T == 0 || n >= (base.sh.nw == 4 ? kCUs + 1 : kManyItems)) return base;
+  // the diagonal crosses the tiles: their work ramps up
+  const bool ramp = j.causal && j.shift < j.sk.T / 2;
   if (j.chunk) {
     // A pair whose two-group launch leaves half the chip idle or more is split
     // (by its sizes alone: its workspace query knows no offsets).  A
     // device's pairs of a zig-zag ring of 8 over 32,768 tokens x 4 heads (2,048
-    // rows each): forward 0.78 -> 0.62 ms, backward 2.75 -> 1.52; over 131,072
-    // (8,192 rows, groups without a split) forward 2.24-2.40 -> 2.35-2.37 on two
-    // streams, which two launches without groups just fill (2.19-2.35), backward
-    // 9.69 -> 7.29; a pair alone 183 -> 105 us.  (Forward and dQ over fewer than
-    // 1,280 keys: no parts, 34 pairs of 768-1,279 keys down to 0.76x.)
+    // rows each): forward 0.78 -> 0.62 ms, backward 2.75 -> 1.52.  (Forward and dQ
+    // over fewer than 1,280 keys: no parts, 34 pairs of 768-1,279 keys down to
+    // 0.76x.)
     const Work w2 = work_of(k, j, shape(2));
     const int least = k == DKDV ? 8 : 10;
     int p = 1;
@@ -546,6 +547,15 @@ Launch pick(Which k, const Job& j, const Launch& base) {
            w2.inner >= (p == 1 ? least : 8 * p))
       p *= 2;
     if (p > 1) return {shape(2), split_of(w2, j, p)};
+    // Two pairs at a time fill each other's last rounds, and groups only cost their
+    // rate, once two launches without groups fill the chip (d = 64: more than
+    // fill, as two of its workgroups share a CU).  Ring of 8, zig-zag, 4 heads,
+    // without / with groups: 131,072 tokens (8,192 rows, 128 workgroups) forward
+    // 2.23 / 2.40 ms, 327,680 (320) 12.5 / 13.7, 638,976 (624) 47.2 / 51.0 and its
+    // last device's backward 152 / 165; 98,304 (96) 1.56 / 1.50.  The pair over
+    // the diagonal evens out its own ramp: with groups (contiguous, 131,072, the
+    // second device 0.98 / 0.84).
+    if (j.launches > 1 && !ramp && (j.sq.d == 64 ? n > kCUs : 2 * n >= kCUs)) return base;
   }
   if (k != DKDV) {
     // Key groups need a few keys each (up to 128 keys 7-15 % slower, from 256 on
@@ -554,14 +564,16 @@ Launch pick(Which k, const Job& j, const Launch& base) {
     // pairs and sequences 0.82-1.00x); nor do they pay for a forward over the
     // diagonal that is much more than a round (2,901 x 32 causal 77 -> 87 us, a
     // 13,542-row pair x 8 360 -> 379; up to 320 workgroups 1.03-1.39x).
-    const bool ramp = j.causal && j.shift < j.sk.T / 2;
     if (j.sk.T < 256) return base;
     if (j.sq.d == 64 && n > kCUs && !ramp) return base;
     if (j.sq.d == 128 && k == FWD && n > kCUs * 5 / 4 && ramp) return base;
   }
   Launch best = base;
   double t = 0.97 * est_unsplit_us(k, j, base.sh);
-  for (int groups = 2; groups <= (k == DKDV ? 2 : 4); groups *= 2) {
+  // (dQ with four groups only on half the chip: 128 to 312 workgroups alone
+  // 0.96-0.99x, and 15 ms for 17 beside another pair)
+  const int most = k == DKDV || (k == DQ && 2 * n > kCUs) ? 2 : 4;
+  for (int groups = 2; groups <= most; groups *= 2) {
     const double e = est_unsplit_us(k, j, shape(groups));
     if (e < t) {
       t = e;
@@ -823,6 +835,7 @@ struct Chunk {
   int tk = 0;          // key/value rows
   int shift = 0;       // query offset - key offset
   int accumulate = 0;  // backward: add to the gradients instead of writing them
+  int launches = 1;    // pairs that the caller runs at a time
 };
 
 pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* cu,
@@ -831,7 +844,7 @@ pdy_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
                     void* workspace, size_t workspace_bytes, void* stream, const Chunk& c,
                     const char* who) {
   pdy_status st;
-  const Job job{s, sk, causal, c.on != 0, c.shift};
+  const Job job{s, sk, causal, c.on != 0, c.shift, c.launches};
   const Launch base = base_launch(FWD, job);
   Launch l = pick(FWD, job, base);
   // (a pair whose workspace was sized for other chunks takes fewer parts)
@@ -902,7 +915,7 @@ pdy_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
                     void* workspace, size_t workspace_bytes, void* stream, const Chunk& c,
                     const char* who, bool fit_splits) {
   pdy_status st;
-  const Job job{s, sk, causal, c.on != 0, c.shift};
+  const Job job{s, sk, causal, c.on != 0, c.shift, c.launches};
   const Launch base_k = base_launch(DKDV, job), base_q = base_launch(DQ, job);
   Launch lk = pick(DKDV, job, base_k), lq = pick(DQ, job, base_q);
   // fit_splits: a workspace of fixed size, or sized for other chunks, takes
@@ -1127,16 +1140,17 @@ pdy_status pdy_launch_shapes(int32_t total_tokens, int32_t num_seqs, int32_t max
 
 pdy_status pdy_chunk_launch_shapes(int32_t tq, int32_t tk, int32_t q_offset, int32_t k_offset,
                                    int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
-                                   int32_t causal, int32_t* shapes) {
+                                   int32_t causal, int32_t launches, int32_t* shapes) {
   g_err[0] = 0;
   Sizes sq, sk;
   pdy_status st;
   if ((st = chunk_sizes(tq, tk, num_heads_q, num_heads_kv, head_dim, &sq, &sk)) != PDY_OK)
     return st;
   if (q_offset < 0 || k_offset < 0) return fail(PDY_ERR_INVALID_ARG, "offsets must be >= 0");
+  if (launches < 1) return fail(PDY_ERR_INVALID_ARG, "launches must be >= 1 (got %d)", launches);
   if (causal != 0 && causal != 1) return fail(PDY_ERR_INVALID_ARG, "causal must be 0 or 1");
   if (shapes == nullptr) return fail(PDY_ERR_INVALID_ARG, "shapes is NULL");
-  write_shapes({sq, sk, causal, true, q_offset - k_offset}, shapes);
+  write_shapes({sq, sk, causal, true, q_offset - k_offset, launches}, shapes);
   return PDY_OK;
 }
 
@@ -1180,12 +1194,23 @@ pdy_status attn_fwd_chunk(const void* q, const void* k, const void* v, int32_t t
                           int32_t num_heads_kv, int32_t head_dim, int32_t causal, float scale,
                           void* o, float* lse, void* workspace, size_t workspace_bytes,
                           void* stream) {
+  return attn_fwd_chunk_shared(q, k, v, tq, tk, q_offset, k_offset, num_heads_q, num_heads_kv,
+                               head_dim, causal, scale, o, lse, workspace, workspace_bytes, stream,
+                               1);
+}
+
+pdy_status attn_fwd_chunk_shared(const void* q, const void* k, const void* v, int32_t tq,
+                                 int32_t tk, int32_t q_offset, int32_t k_offset,
+                                 int32_t num_heads_q, int32_t num_heads_kv, int32_t head_dim,
+                                 int32_t causal, float scale, void* o, float* lse, void* workspace,
+                                 size_t workspace_bytes, void* stream, int32_t launches) {
   g_err[0] = 0;
   Sizes sq, sk;
   pdy_status st;
   if ((st = chunk_sizes(tq, tk, num_heads_q, num_heads_kv, head_dim, &sq, &sk)) != PDY_OK)
     return st;
   if (q_offset < 0 || k_offset < 0) return fail(PDY_ERR_INVALID_ARG, "offsets must be >= 0");
+  if (launches < 1) return fail(PDY_ERR_INVALID_ARG, "launches must be >= 1 (got %d)", launches);
   if ((st = check_scale(scale, causal)) != PDY_OK) return st;
   if (tq == 0) return PDY_OK;
   if ((st = check_ptr(q, "q")) || (st = check_ptr(o, "o")) || (st = check_ptr(lse, "lse")) ||
@@ -1196,6 +1221,7 @@ pdy_status attn_fwd_chunk(const void* q, const void* k, const void* v, int32_t t
   c.on = 1;
   c.tk = tk;
   c.shift = q_offset - k_offset;
+  c.launches = launches;
   return fwd_impl(q, k, v, nullptr, sq, sk, causal, scale, o, lse, workspace, workspace_bytes, stream,
                   c, "attn_fwd_chunk");
 }
@@ -1252,12 +1278,25 @@ pdy_status attn_bwd_chunk(const void* q, const void* k, const void* v, const voi
                           int32_t num_heads_kv, int32_t head_dim, int32_t causal, float scale,
                           float* dq, float* dk, float* dv, int32_t accumulate, void* workspace,
                           size_t workspace_bytes, void* stream) {
+  return attn_bwd_chunk_shared(q, k, v, o, lse, dout, tq, tk, q_offset, k_offset, num_heads_q,
+                               num_heads_kv, head_dim, causal, scale, dq, dk, dv, accumulate,
+                               workspace, workspace_bytes, stream, 1);
+}
+
+pdy_status attn_bwd_chunk_shared(const void* q, const void* k, const void* v, const void* o,
+                                 const float* lse, const void* dout, int32_t tq, int32_t tk,
+                                 int32_t q_offset, int32_t k_offset, int32_t num_heads_q,
+                                 int32_t num_heads_kv, int32_t head_dim, int32_t causal,
+                                 float scale, float* dq, float* dk, float* dv, int32_t accumulate,
+                                 void* workspace, size_t workspace_bytes, void* stream,
+                                 int32_t launches) {
   g_err[0] = 0;
   Sizes sq, sk;
   pdy_status st;
   if ((st = chunk_sizes(tq, tk, num_heads_q, num_heads_kv, head_dim, &sq, &sk)) != PDY_OK)
     return st;
   if (q_offset < 0 || k_offset < 0) return fail(PDY_ERR_INVALID_ARG, "offsets must be >= 0");
+  if (launches < 1) return fail(PDY_ERR_INVALID_ARG, "launches must be >= 1 (got %d)", launches);
   if ((st = check_scale(scale, causal)) != PDY_OK) return st;
   if (tq == 0 && tk == 0) return PDY_OK;
   if (tq > 0 && ((st = check_ptr(q, "q")) || (st = check_ptr(o, "o")) ||
@@ -1288,6 +1327,7 @@ pdy_status attn_bwd_chunk(const void* q, const void* k, const void* v, const voi
   c.tk = tk;
   c.shift = q_offset - k_offset;
   c.accumulate = accumulate;
+  c.launches = launches;
   return bwd_impl(q, k, v, o, lse, dout, nullptr, sq, sk, causal, scale, dq, dk, dv, workspace,
                   workspace_bytes, stream, c, "attn_bwd_chunk", /*fit_splits=*/true);
 }

@@ -24,7 +24,7 @@ PDY_ERR_HIP = -4
 # exported symbols, in the order include/pdyattn.h declares them
 SYMBOLS = ("attn_fwd_workspace_size", "attn_bwd_workspace_size", "attn_fwd", "attn_bwd",
            "attn_fwd_chunk_workspace_size", "attn_bwd_chunk_workspace_size", "attn_fwd_chunk",
-           "attn_bwd_chunk", "attn_merge",
+           "attn_bwd_chunk", "attn_fwd_chunk_shared", "attn_bwd_chunk_shared", "attn_merge",
            "attn_validate_cu_seqlens", "attn_bwd_noalloc", "pdy_launch_shapes",
            "pdy_chunk_launch_shapes", "pdy_status_string", "pdy_last_error",
            "pdy_kernel_count", "pdy_kernel_name", "pdy_profile_start", "pdy_profile_stop")
@@ -69,6 +69,10 @@ def lib() -> ctypes.CDLL:
     L.attn_bwd_chunk.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, i32,
                                  f32, vp, vp, vp, i32, vp, sz, vp]
     L.attn_bwd_chunk.restype = i32
+    L.attn_fwd_chunk_shared.argtypes = L.attn_fwd_chunk.argtypes + [i32]
+    L.attn_fwd_chunk_shared.restype = i32
+    L.attn_bwd_chunk_shared.argtypes = L.attn_bwd_chunk.argtypes + [i32]
+    L.attn_bwd_chunk_shared.restype = i32
     L.attn_merge.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp, vp, vp]
     L.attn_merge.restype = i32
     L.attn_validate_cu_seqlens.argtypes = [vp, i32, i32, ctypes.POINTER(i32), vp]
@@ -78,7 +82,7 @@ def lib() -> ctypes.CDLL:
     L.attn_bwd_noalloc.restype = i32
     L.pdy_launch_shapes.argtypes = [i32] * 7 + [ctypes.POINTER(i32)]
     L.pdy_launch_shapes.restype = i32
-    L.pdy_chunk_launch_shapes.argtypes = [i32] * 8 + [ctypes.POINTER(i32)]
+    L.pdy_chunk_launch_shapes.argtypes = [i32] * 9 + [ctypes.POINTER(i32)]
     L.pdy_chunk_launch_shapes.restype = i32
     L.pdy_status_string.argtypes = [i32]
     L.pdy_status_string.restype = ctypes.c_char_p
@@ -138,11 +142,12 @@ def launch_shapes(total_tokens, num_seqs, max_seqlen, hq, hkv, d, causal: bool =
                                            int(bool(causal)), out), "pdy_launch_shapes", out)
 
 
-def chunk_launch_shapes(tq, tk, q_offset, k_offset, hq, hkv, d, causal: bool = True) -> dict:
+def chunk_launch_shapes(tq, tk, q_offset, k_offset, hq, hkv, d, causal: bool = True,
+                        launches: int = 1) -> dict:
     """The same for attn_fwd_chunk and attn_bwd_chunk."""
     out = (ctypes.c_int32 * 9)()
     return _shapes(lib().pdy_chunk_launch_shapes(tq, tk, q_offset, k_offset, hq, hkv, d,
-                                                 int(bool(causal)), out),
+                                                 int(bool(causal)), launches, out),
                    "pdy_chunk_launch_shapes", out)
 
 
@@ -313,9 +318,11 @@ def _ptr(t):
 
 
 def attn_fwd_chunk(q, k, v, q_offset: int, k_offset: int, causal: bool = True,
-                   scale: Optional[float] = None, out=None, lse=None, workspace=None):
+                   scale: Optional[float] = None, out=None, lse=None, workspace=None,
+                   launches: int = 1):
     """Partial O [Tq, Hq, d] bf16 and LSE [Hq, Tq] fp32 of the query chunk at
-    positions q_offset.. over the key/value chunk at positions k_offset.."""
+    positions q_offset.. over the key/value chunk at positions k_offset..;
+    launches: how many such calls the caller runs at a time."""
     import torch
     _check_tensor(q, "q", torch.bfloat16, 3)
     _check_tensor(k, "k", torch.bfloat16, 3)
@@ -332,21 +339,22 @@ def attn_fwd_chunk(q, k, v, q_offset: int, k_offset: int, causal: bool = True,
         lse = torch.empty((hq, tq), dtype=torch.float32, device=q.device)
     if workspace is None:
         workspace = _ws(fwd_chunk_workspace_size(tq, tk, hq, hkv, d), q.device)
-    st = lib().attn_fwd_chunk(q.data_ptr(), _ptr(k) if tk else 0, _ptr(v) if tk else 0, tq, tk,
-                              int(q_offset), int(k_offset), hq, hkv, d, int(bool(causal)),
-                              float(scale), out.data_ptr(), lse.data_ptr(), workspace.data_ptr(),
-                              workspace.numel() * workspace.element_size(),
-                              _stream_handle(q.device))
+    st = lib().attn_fwd_chunk_shared(
+        q.data_ptr(), _ptr(k) if tk else 0, _ptr(v) if tk else 0, tq, tk, int(q_offset),
+        int(k_offset), hq, hkv, d, int(bool(causal)), float(scale), out.data_ptr(),
+        lse.data_ptr(), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+        _stream_handle(q.device), int(launches))
     _check(st, "attn_fwd_chunk")
     return out, lse
 
 
 def attn_bwd_chunk(q, k, v, o, lse, dout, q_offset: int, k_offset: int, causal: bool = True,
                    scale: Optional[float] = None, dq=None, dk=None, dv=None, workspace=None,
-                   accumulate: bool = False):
+                   accumulate: bool = False, launches: int = 1):
     """This (query chunk, key chunk) pair's part of dQ [Tq, Hq, d] and dK, dV
     [Tk, Hkv, d] (fp32), given the final o and lse of the query rows; with
-    accumulate=True it is added to the given dq, dk, dv."""
+    accumulate=True it is added to the given dq, dk, dv.  launches: how many
+    such calls the caller runs at a time."""
     import torch
     for t, name in ((q, "q"), (k, "k"), (v, "v"), (o, "o"), (dout, "dout")):
         _check_tensor(t, name, torch.bfloat16, 3)
@@ -364,12 +372,11 @@ def attn_bwd_chunk(q, k, v, o, lse, dout, q_offset: int, k_offset: int, causal: 
         dv = torch.empty((tk, hkv, d), dtype=torch.float32, device=dev)
     if workspace is None:
         workspace = _ws(bwd_chunk_workspace_size(tq, tk, hq, hkv, d), dev)
-    st = lib().attn_bwd_chunk(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                              lse.data_ptr(), dout.data_ptr(), tq, tk, int(q_offset),
-                              int(k_offset), hq, hkv, d, int(bool(causal)), float(scale),
-                              dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), int(bool(accumulate)),
-                              workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                              _stream_handle(dev))
+    st = lib().attn_bwd_chunk_shared(
+        q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), dout.data_ptr(),
+        tq, tk, int(q_offset), int(k_offset), hq, hkv, d, int(bool(causal)), float(scale),
+        dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), int(bool(accumulate)), workspace.data_ptr(),
+        workspace.numel() * workspace.element_size(), _stream_handle(dev), int(launches))
     _check(st, "attn_bwd_chunk")
     return dq, dk, dv
 

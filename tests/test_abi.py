@@ -140,7 +140,10 @@ def test_launch_shapes():
     assert set(P.launch_shapes(0, 1, 0, 4, 4, 128).values()) == {(0, 0, 0)}
     c = P.chunk_launch_shapes(64, 0, 0, 0, 4, 4, 128)
     assert c["bwd_dkdv_kernel"] == (0, 0, 0) and c["fwd_kernel"][0] > 0
+    assert P.lib().attn_fwd_chunk_shared(FAKE, FAKE, FAKE, 64, 64, 0, 0, 4, 4, 128, 1, 0.1, FAKE,
+                                         FAKE, FAKE, 1 << 20, None, 0) == P.PDY_ERR_INVALID_ARG
     for call in (lambda: P.launch_shapes(512, 1, 500, 8, 8, 128),
+                 lambda: P.chunk_launch_shapes(512, 512, 0, 0, 8, 8, 128, launches=0),
                  lambda: P.launch_shapes(512, 1, 512, 8, 8, 96),
                  lambda: P.chunk_launch_shapes(512, 512, -1, 0, 8, 8, 128)):
         with pytest.raises(P.PdyError):

@@ -86,3 +86,32 @@ def test_single_sequences(T, hq, hkv, d, causal, fwd, dq, dkdv):
 ])
 def test_pairs(tq, tk, qo, d, fwd):
     assert P.chunk_launch_shapes(tq, tk, qo, 0, 4, 4, d)["fwd_kernel"] == fwd
+
+
+@pytest.mark.parametrize("rows,heads,d,alone,two", [
+    # (forward, dQ, dK/dV groups of a fully visible pair) alone and two at a time:
+    # groups go where two launches fill the chip without them
+    (6144, 4, 128, (2, 2, 2), (2, 2, 2)),     # 96 workgroups
+    (8192, 4, 128, (2, 2, 2), (1, 1, 1)),     # 128
+    (39936, 4, 128, (2, 2, 2), (1, 1, 1)),    # 624
+    (8192, 4, 64, (2, 2, 2), (2, 2, 2)),      # 128, but two to a CU
+    (20480, 4, 64, (1, 1, 2), (1, 1, 1)),     # 320
+])
+def test_pairs_two_at_a_time(rows, heads, d, alone, two):
+    for launches, expect in ((1, alone), (2, two)):
+        got = P.chunk_launch_shapes(rows, rows, rows, 0, heads, heads, d, launches=launches)
+        assert tuple(s[1] for s in got.values()) == expect, (launches, got)
+        assert all(s[2] == 1 for s in got.values())
+
+
+def test_diagonal_pair_keeps_its_groups():
+    for launches in (1, 2):
+        got = P.chunk_launch_shapes(16384, 16384, 16384, 16384, 4, 4, 128, launches=launches)
+        assert {s[1] for s in got.values()} == {2}
+
+
+def test_dq_takes_no_four_groups_on_more_than_half_the_chip():
+    got = P.chunk_launch_shapes(19968, 19968, 0, 0, 2, 2, 128, causal=False)   # 156 workgroups
+    assert got["bwd_dq_kernel"][1] < 4
+    got = P.chunk_launch_shapes(1000, 900, 4096, 0, 4, 4, 128)                 # 32
+    assert got["bwd_dq_kernel"][1] == 4
