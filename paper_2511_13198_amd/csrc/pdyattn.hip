@@ -570,9 +570,11 @@ Launch pick(Which k, const Job& j, const Launch& base) {
   }
   Launch best = base;
   double t = 0.97 * est_unsplit_us(k, j, base.sh);
-  // (dQ with four groups only on half the chip: 128 to 312 workgroups alone
-  // 0.96-0.99x, and 15 ms for 17 beside another pair)
-  const int most = k == DKDV || (k == DQ && 2 * n > kCUs) ? 2 : 4;
+  // (8-wave dQ takes four groups only on half the chip: 128 to 312 workgroups
+  // alone 0.96-0.99x, and 15 ms for 17 beside another pair.  4-wave ones keep
+  // them up to a round: against two groups 1,789 tokens x 12 heads of 64 1.12x,
+  // 1,104 x 16 1.06x, 2,048 x 16 1.00x, 1,024 x 32 0.94x.)
+  const int most = k == DKDV || (k == DQ && base.sh.nw == 8 && 2 * n > kCUs) ? 2 : 4;
   for (int groups = 2; groups <= most; groups *= 2) {
     const double e = est_unsplit_us(k, j, shape(groups));
     if (e < t) {

@@ -70,6 +70,10 @@ def test_d64_four_wave_query_tiles(lengths, hq, fwd, dq):
     # 4-wave query tiles at d = 64: dQ with few heads up to two rounds
     (38243, 4, 4, 64, True, (4, 1, 1), (8, 1, 1), (8, 1, 1)),
     (17045, 8, 8, 64, True, (4, 1, 1), (4, 1, 1), (8, 1, 1)),
+    # 4-wave dQ up to a round (168 and 256 workgroups): four groups; beyond: none
+    (1789, 12, 4, 64, True, (8, 4, 1), (8, 4, 1), (8, 2, 8)),
+    (2048, 16, 16, 128, True, (8, 4, 1), (8, 4, 1), (8, 2, 1)),
+    (2048, 17, 17, 128, True, (4, 1, 1), (4, 1, 1), (8, 2, 1)),
 ])
 def test_single_sequences(T, hq, hkv, d, causal, fwd, dq, dkdv):
     got = shapes([T], hq, hkv, d, causal)
