@@ -431,6 +431,17 @@ double est_unsplit_us(Which k, const Job& j, const Shape& sh) {
   return whole * kWorkgroupUs + units * unit * (j.sq.d == 64 ? 0.7 : 1.0);
 }
 
+// What two groups of half as many parts save in partial results (and the
+// combining launch where none are left), as a share of a split launch's time.
+double saved_share(const Launch& base, const Work& w, const Job& j) {
+  constexpr double kMovedBytesPerUs = 5.0e6;
+  const int p = split_parts(w.items * w.heads, w.inner, w.unit_us, w.slice);
+  const double longest = base.split.cap ? base.split.cap : (double)((w.inner + p - 1) / p);
+  const double mean = (double)(w.items * w.heads) / kCUs * w.inner * (j.causal ? 0.5 : 1.0);
+  return (p * w.slice / kMovedBytesPerUs + (p == 2 ? kLaunchUs : 0.0)) /
+         (std::max(longest, mean) * w.unit_us);
+}
+
 constexpr int64_t kAverageShort = 512;
 
 // launches of this many workgroups fill the chip in any shape
@@ -477,10 +488,14 @@ Launch pick(Which k, const Job& j, const Launch& base) {
     //     60 of 1,024 56 -> 74 (d = 64: 40 -> 56), 100 of 512 37 -> 41, 30 of 2,048
     //     without a mask 131 -> 142, 10 of up to 154 x 16 18 -> 22.  Two parts:
     //     always, without parts (47 random ones 1.27x): 16 of 2,048 74.8 -> 60.2,
-    //     15 of 4,096 247 -> 222.  Four parts, with half as many: at d = 128 with
-    //     at most two query heads a key head, over a quarter to 7/8 of a round (21
-    //     random ones 1.08x); elsewhere the products' lower rate outweighs it (d =
-    //     64: 70 random ones 0.99x, as low as 0.85; 3 of 16,384 297 -> 315).
+    //     15 of 4,096 247 -> 222.  Four parts, with half as many: where the partial
+    //     results' share of the time is at least 0.2 (d = 128: of 263 random ones
+    //     124 1.07x, 8 slower, the rest would be 0.996x) or 0.3 (d = 64, whose
+    //     products lose more: of 276, 86 1.04x, 11 slower), so mostly short segments
+    //     with many rows: 11 of 16-103 tokens x 32/8 heads 50.9 -> 45.5, 42 of 30-828
+    //     x 9/3 175 -> 158; 3 of 16,384 x 1 of 64 297 -> 315.  Not where the four
+    //     parts fit two rounds and the two-group workgroups fill both as well (8 of
+    //     3,961 x 1 0.86x).
     if (k != DKDV) return base;
     const Shape four{4, 1};
     if (j.sk.maxlen <= kShortSeg && j.sk.T <= kAverageShort * j.sk.N &&
@@ -491,8 +506,8 @@ Launch pick(Which k, const Job& j, const Launch& base) {
     const int64_t n2 = w2.items * w2.heads;
     const int p = base.split.parts;
     if (p == 1 ? n2 > kCUs || w.inner < 4
-               : p > 2 && (j.sq.d == 64 || j.sq.hq > 2 * j.sq.hkv || n2 < kCUs / 4 ||
-                           n2 > kCUs * 7 / 8))
+               : p > 2 && (saved_share(base, w, j) < (j.sq.d == 64 ? 0.3 : 0.2) ||
+                           (n <= kCUs / 2 && n2 >= kCUs * 7 / 8)))
       return base;
     return {shape(2), split_of(w2, j, std::max(1, p / 2))};
   }
@@ -516,13 +531,9 @@ Launch pick(Which k, const Job& j, const Launch& base) {
     static constexpr double kShare[2][3][3] = {
         {{0, kNever, 0.12}, {0, kNever, 0.10}, {0.13, 0.25, 0.16}},
         {{0.11, 0.18, 0.17}, {0.05, 0.08, 0.08}, {0.05, 0.11, 0.05}}};
-    constexpr double kMovedBytesPerUs = 5.0e6;
     const int p = split_parts(n, w.inner, w.unit_us, w.slice);
-    const double longest = base.split.cap ? base.split.cap : (double)((w.inner + p - 1) / p);
-    const double mean = (double)n / kCUs * w.inner * (j.causal ? 0.5 : 1.0);
-    const double us = std::max(longest, mean) * w.unit_us;
-    const double saved_us = p * w.slice / kMovedBytesPerUs + (p == 2 ? kLaunchUs : 0.0);
-    if (kShare[j.sq.d == 128][k][p == 2 ? 0 : base.split.cap ? 2 : 1] * us > saved_us) return base;
+    if (saved_share(base, w, j) < kShare[j.sq.d == 128][k][p == 2 ? 0 : base.split.cap ? 2 : 1])
+      return base;
     const Work w2 = work_of(k, j, shape(2));
     if (p == 2 && j.sq.d == 64 && k != DKDV &&
         (!j.causal || 10 * w2.items * w2.heads > 21 * kCUs))

@@ -46,7 +46,9 @@ GROUP_CASES = [
     ([2304], 4, 4, 128, False, [(8, 2, 2), (8, 2, 2), (8, 2, 2)]),
     # packed: dK/dV over 128-key tiles
     ([600, 1, 129, 1024] * 4, 3, 3, 128, True, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
-    ([2048, 1000, 2000], 4, 2, 128, True, [(4, 1, 2), (4, 1, 2), (8, 2, 2)]),
+    ([2048, 1000, 2000], 4, 2, 128, True, [(4, 1, 2), (4, 1, 2), (8, 1, 4)]),
+    ([1800, 1700, 1500], 4, 4, 128, True, [(4, 1, 1), (4, 1, 2), (8, 2, 2)]),
+    ([103, 52] * 5, 32, 8, 64, True, [(4, 1, 1), (4, 1, 1), (8, 2, 2)]),
     ([300, 1, 129, 512], 2, 1, 64, True, [(4, 1, 1), (4, 1, 1), (8, 1, 4)]),
     ([300, 0, 127], 4, 4, 128, False, [(4, 1, 1), (4, 1, 1), (8, 2, 1)]),
     # d = 64: 300 8-wave tiles, so a 4-wave forward
@@ -77,7 +79,8 @@ def test_short_segments_full_parity(lengths, hq, hkv, d, causal):
 
 @pytest.mark.parametrize("nseg,hi,rest,hq,d,scheduled", [
     # segment-major: to 64 segments and 16,384 segments x workgroups
-    (2, 4000, 4000, 1, 128, False), (64, 1100, 100, 2, 64, False), (65, 1100, 100, 2, 64, True),
+    (2, 4000, 4000, 1, 128, False), (48, 1100, 100, 2, 64, False), (65, 1100, 100, 2, 64, True),
+    (64, 1100, 100, 2, 64, True),    # dK/dV in two parts of 128-key tiles beyond them
     (64, 1100, 1100, 2, 64, True),
     (48, 2841, 1300, 1, 64, True),   # within them but for its parts
     # level-major: to 128 segments

@@ -22,11 +22,14 @@ def shapes(lengths, hq, hkv, d, causal):
     # two parts: two groups without parts
     ([2048] * 16, 1, 1, 64, True, (8, 2, 1)),
     ([4096] * 15, 1, 1, 128, False, (8, 2, 1)),
-    # four parts: at d = 128, on both sides of the lines
+    # four parts: by the share of time that their partial results take
     ([2048] * 4, 2, 2, 128, True, (8, 2, 2)),
     ([2048] * 4, 8, 2, 128, True, (8, 1, 4)),
-    ([2048] * 4, 2, 2, 64, True, (8, 1, 4)),
-    ([2048] * 3, 1, 1, 128, True, (8, 1, 4)),
+    ([2048] * 4, 2, 2, 64, True, (8, 2, 2)),
+    ([2048] * 3, 4, 2, 64, True, (8, 1, 4)),
+    ([103, 52] * 5, 32, 8, 128, True, (8, 2, 2)),
+    ([103, 52] * 5, 32, 8, 64, True, (8, 2, 2)),
+    ([828] * 4 + [207] * 38, 9, 3, 128, True, (8, 2, 2)),
     ([4096] * 8, 1, 1, 128, True, (8, 1, 4)),
     ([16384] * 3, 1, 1, 64, True, (8, 1, 4)),
 ])
